@@ -339,7 +339,7 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
         return MLS_E_NOMEM;
     }
     if (hipMalloc((void **)&c.err, sizeof(ErrWord)) != hipSuccess ||
-        hipMalloc((void **)&c.stats, sizeof(DevStats)) != hipSuccess ||
+        hipMalloc((void **)&c.stats, kStatSlots * sizeof(DevStats)) != hipSuccess ||
         hipMalloc((void **)&c.work, 128 * sizeof(uint32_t)) != hipSuccess ||
         hipMalloc((void **)&c.step_ctr, sizeof(unsigned long long)) != hipSuccess) {
         mls_ctx_destroy(ctx);
@@ -347,7 +347,7 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
     }
     const unsigned long long none = kNoError;
     hipMemcpy(c.err, &none, sizeof(none), hipMemcpyHostToDevice);
-    hipMemset(c.stats, 0, sizeof(DevStats));
+    hipMemset(c.stats, 0, kStatSlots * sizeof(DevStats));
     hipMemset(c.work, 0, 128 * sizeof(uint32_t));
     hipMemset(c.step_ctr, 0, sizeof(unsigned long long));
     const mls_status ts = setup_tiles(c, want_tile);
@@ -658,8 +658,14 @@ mls_status mls_stats_get(mls_ctx *ctx, mls_stats *out)
     if (!ctx || !out) return MLS_E_ARG;
     Ctx &c = ctx->c;
     if (hipDeviceSynchronize() != hipSuccess) return MLS_E_HIP;
-    DevStats d;
-    if (hipMemcpy(&d, c.stats, sizeof(d), hipMemcpyDeviceToHost) != hipSuccess) return MLS_E_HIP;
+    DevStats slot[kStatSlots], d = {};
+    if (hipMemcpy(slot, c.stats, sizeof(slot), hipMemcpyDeviceToHost) != hipSuccess) return MLS_E_HIP;
+    for (const DevStats &q : slot) {
+        d.fp64_solves += q.fp64_solves;
+        d.fallbacks += q.fallbacks;
+        d.learned += q.learned;
+        d.kappa_max_bits = std::max(d.kappa_max_bits, q.kappa_max_bits);
+    }
     out->fp64_solves = (int64_t)d.fp64_solves;
     out->fallbacks = (int64_t)d.fallbacks;
     out->learned = (int64_t)d.learned;
@@ -678,7 +684,7 @@ mls_status mls_stats_reset(mls_ctx *ctx)
 {
     if (!ctx) return MLS_E_ARG;
     if (hipDeviceSynchronize() != hipSuccess) return MLS_E_HIP;
-    return hipMemset(ctx->c.stats, 0, sizeof(DevStats)) == hipSuccess ? MLS_OK : MLS_E_HIP;
+    return hipMemset(ctx->c.stats, 0, kStatSlots * sizeof(DevStats)) == hipSuccess ? MLS_OK : MLS_E_HIP;
 }
 
 mls_status mls_fast_tables(mls_ctx *ctx, float *dst, int64_t *count, int32_t *row_stride, int32_t first[2],

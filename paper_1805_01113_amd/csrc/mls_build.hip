@@ -87,15 +87,7 @@ k_build_exact(const Grid *__restrict__ gp, const Weight W, float tau, int64_t n,
         float ph[kNe];
         exact_from_geo(g, W, tau, c, l, px, py, pz, G, out, rout, 0, err, routed, kmax, ph);
     }
-    // one atomic per wavefront for the statistics
-    unsigned long long tot = routed;
-    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off);
-    float km = kmax;
-    for (int off = 32; off > 0; off >>= 1) km = fmaxf(km, __shfl_xor(km, off));
-    if (lane == 0) {
-        if (tot) atomicAdd(&st->fp64_solves, tot);
-        if (km > 0.f) atomicMax(&st->kappa_max_bits, __float_as_uint(km));
-    }
+    wave_stats(st, routed, kmax);
 }
 
 // Exact build fused with the interpolation (eq. 6) and the direct forcing of
@@ -239,14 +231,7 @@ k_build_interp(const Grid *__restrict__ gp, const Weight W, float tau, int64_t n
         const bool counted = valid && ok && (NF == 0 || !fp64);
         wave_key_max(tmax + c * tstride, counted ? (int64_t)tile_from_geo(g, c, G) : -1, finite_abs(cfv));
     }
-    unsigned long long tot = routed;
-    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off);
-    float km = kmax;
-    for (int off = 32; off > 0; off >>= 1) km = fmaxf(km, __shfl_xor(km, off));
-    if (lane == 0) {
-        if (tot) atomicAdd(&st->fp64_solves, tot);
-        if (km > 0.f) atomicMax(&st->kappa_max_bits, __float_as_uint(km));
-    }
+    wave_stats(st, routed, kmax);
 }
 
 // Zeroes n words (a kernel rather than a memset node, for graph capture).

@@ -730,6 +730,21 @@ __device__ __forceinline__ void wave_key_max(uint32_t *tmax, int64_t key, float 
     }
 }
 
+// End-of-kernel statistics of one wavefront (every lane calls it): the lanes'
+// FP64 solves and the largest condition bound into the workgroup's copy.
+__device__ __forceinline__ DevStats &stat_slot(DevStats *st) { return st[blockIdx.x % kStatSlots]; }
+
+__device__ __forceinline__ void wave_stats(DevStats *st, unsigned long long routed, float kmax)
+{
+    for (int off = 32; off > 0; off >>= 1) routed += __shfl_xor(routed, off);
+    for (int off = 32; off > 0; off >>= 1) kmax = fmaxf(kmax, __shfl_xor(kmax, off));
+    if ((threadIdx.x & 63) == 0) {
+        DevStats &d = stat_slot(st);
+        if (routed) atomicAdd(&d.fp64_solves, routed);
+        if (kmax > 0.f) atomicMax(&d.kappa_max_bits, __float_as_uint(kmax));
+    }
+}
+
 // |v| when finite, else 0 (a non-finite value is reported where it is used).
 __device__ __forceinline__ float finite_abs(float v)
 {

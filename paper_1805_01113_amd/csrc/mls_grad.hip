@@ -201,7 +201,7 @@ __device__ __forceinline__ bool interp_grad_fp64(const Grid &g, const Weight &Wt
 
 __device__ __forceinline__ void count_fp64(DevStats *stats, unsigned long long routed)
 {
-    if (routed) atomicAdd(&stats->fp64_solves, routed);
+    if (routed) atomicAdd(&stat_slot(stats).fp64_solves, routed);
 }
 
 // FP64 queue: q[0] = entries, q[1 + i] = 4 l + c.

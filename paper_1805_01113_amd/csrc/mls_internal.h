@@ -77,7 +77,14 @@ struct ErrWord {
     unsigned long long word;
 };
 
-struct DevStats {
+// Statistics of the build kernels, spread over kStatSlots copies of one cache
+// line each (workgroup b updates copy b % kStatSlots; mls_stats_get combines
+// them).  Atomics on one address are served one after another, about 12 ns
+// each: with a single copy, one update per wavefront of a 32768-wavefront
+// build took 0.33-0.39 ms, more than the rest of the kernel on a million
+// markers.
+constexpr int kStatSlots = 128;
+struct alignas(128) DevStats {
     unsigned long long fp64_solves;
     unsigned long long fallbacks;
     unsigned long long learned;

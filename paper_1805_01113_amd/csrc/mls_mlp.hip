@@ -627,15 +627,11 @@ k_build_learned(const Grid *__restrict__ gp, const Weight W, float tau, float to
             asm volatile("" ::: "memory");
         }
     }
-    unsigned long long tot = routed;
-    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off);
-    float km = kmax;
-    for (int off = 32; off > 0; off >>= 1) km = fmaxf(km, __shfl_xor(km, off));
+    wave_stats(st, routed, kmax);
     if (lane == 0) {
-        if (tot) atomicAdd(&st->fp64_solves, tot);
-        if (n_fb) atomicAdd(&st->fallbacks, n_fb);
-        if (n_ok) atomicAdd(&st->learned, n_ok);
-        if (km > 0.0f) atomicMax(&st->kappa_max_bits, __float_as_uint(km));
+        DevStats &d = stat_slot(st);
+        if (n_fb) atomicAdd(&d.fallbacks, n_fb);
+        if (n_ok) atomicAdd(&d.learned, n_ok);
     }
 }
 
