@@ -340,7 +340,7 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
     }
     if (hipMalloc((void **)&c.err, sizeof(ErrWord)) != hipSuccess ||
         hipMalloc((void **)&c.stats, kStatSlots * sizeof(DevStats)) != hipSuccess ||
-        hipMalloc((void **)&c.work, 128 * sizeof(uint32_t)) != hipSuccess ||
+        hipMalloc((void **)&c.work, kWorkWords * sizeof(uint32_t)) != hipSuccess ||
         hipMalloc((void **)&c.step_ctr, sizeof(unsigned long long)) != hipSuccess) {
         mls_ctx_destroy(ctx);
         return MLS_E_NOMEM;
@@ -348,7 +348,7 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
     const unsigned long long none = kNoError;
     hipMemcpy(c.err, &none, sizeof(none), hipMemcpyHostToDevice);
     hipMemset(c.stats, 0, kStatSlots * sizeof(DevStats));
-    hipMemset(c.work, 0, 128 * sizeof(uint32_t));
+    hipMemset(c.work, 0, kWorkWords * sizeof(uint32_t));
     hipMemset(c.step_ctr, 0, sizeof(unsigned long long));
     const mls_status ts = setup_tiles(c, want_tile);
     if (ts != MLS_OK) { mls_ctx_destroy(ctx); return ts; }

@@ -28,6 +28,12 @@ template <int NF>
 constexpr int kCoefStride = NF == 7 ? 8 : 16;
 constexpr uint32_t kMaskI = (1u << kPackI) - 1, kMaskJ = (1u << kPackJ) - 1;
 
+// Colour-list work of the spreading: sizes of the 27 active-tile lists, then
+// kShards claim cursors per colour, each on a 128-byte line of its own.
+constexpr int kShards = 8;
+constexpr __host__ __device__ int kCursor(int colour, int shard) { return 64 + (colour * kShards + shard) * 32; }
+constexpr int kWorkWords = 64 + 27 * kShards * 32;
+
 // One axis of the Eulerian grid as the device sees it.
 struct Axis {
     int32_t n;          // cells
@@ -181,7 +187,7 @@ struct Ctx {
     uint64_t scratch_gen = 0;          // bumped whenever context scratch moves or the tiling changes
                                        // (a captured step graph holds the old addresses and tiling)
     int64_t cf_stride = 0;             // cap_markers rounded up to 64
-    uint32_t *work = nullptr;          // [0..26] active-list sizes per colour, [32..58] cursors
+    uint32_t *work = nullptr;          // kWorkWords: active-list sizes per colour and claim cursors
     int64_t colour_tiles[27] = {};     // tiles of each colour
     // launch shapes (autotuned): resident workgroups per compute unit
     int spread_blocks_per_cu = 16;      // effective (bounded by the LDS of the tile boxes)

@@ -297,7 +297,8 @@ __global__ void __launch_bounds__(kBlock) k_scan_final(const uint32_t *__restric
             tmax[2 * tstride + i] = 0u;
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x < 64) work[threadIdx.x] = 0u;   // colour list sizes and cursors
+    if (blockIdx.x == 0)
+        for (int q = threadIdx.x; q < kWorkWords; q += kBlock) work[q] = 0u;   // colour list sizes and cursors
 }
 
 __device__ __forceinline__ int axis_colour(const Grid &g, int d, int t)
@@ -478,35 +479,47 @@ k_spread_colour(const Grid *__restrict__ gp, int colour, const uint32_t *__restr
     const Axis &AX = g.ax[0], &AY = g.ax[1], &AZ = g.ax[2];
     const int bx = BX > 0 ? BX : g.box[0], by = g.box[1], bz = g.box[2];
     const int bnodes = bx * by * bz;
-    const float inv_by = 1.0f / (float)by;
-    const int64_t abase = g.colour_base[colour];
-    const uint32_t nact = (uint32_t)min((int64_t)work[colour], colour_end(g, colour) - abase);
-    __shared__ int64_t tile_sh;
-    // The box is cleared once here; afterwards every flush returns the nodes
-    // it reads to zero, so each component and tile starts from a clear box.
-    for (int q = threadIdx.x; q < bnodes; q += blockDim.x) acc[q] = 0ull;
     // box-local coordinates of a node index without integer division: with
     // fewer than 2^22 nodes, (q + 1/2) times the FP32 reciprocal of the divisor
     // stays within 1/2 of a quotient's interval from its floor
+    const float inv_by = 1.0f / (float)by;
     const float inv_bx = 1.0f / (float)bx, inv_bxy = 1.0f / (float)(bx * by);
-    // Tiles are claimed through one device-wide counter, whose atomics are
-    // served one after another.  A colour with only a few tiles per workgroup
-    // would have every workgroup queue on it at the start, and the last one to
-    // get its tile sets the launch's end; there the first round is handed out
-    // by position (tile b to workgroup b) and only the rest is claimed.
+    const int64_t abase = g.colour_base[colour];
+    const uint32_t nact = (uint32_t)min((int64_t)work[colour], colour_end(g, colour) - abase);
+    __shared__ int64_t unit_sh;
+    // Work units of a launch: a colour with fewer tiles than workgroups is cut
+    // into its (tile, component) pairs, so that a tile's three components run
+    // side by side; else a unit is a whole tile.
     const uint32_t G = gridDim.x;
-    const uint32_t nfixed = nact < 4u * G ? min(nact, G) : 0u;
-    bool first = true;
-    for (;;) {
-        if (threadIdx.x == 0) {
-            const uint32_t i = first && blockIdx.x < nfixed ? blockIdx.x : nfixed + atomicAdd(&work[32 + colour], 1u);
-            first = false;
-            const int64_t t = i < nact ? (int64_t)active[abase + i] : -1;
-            tile_sh = t < g.ntiles ? t : -1;
+    const bool split = nact <= G;
+    const uint32_t units = split ? 3u * nact : nact;
+    // Workgroup b starts with unit b and ends there if the first round covers
+    // all units; further units are claimed.  Atomics on one address are served
+    // one after another (about 12 ns each), so with a single counter the
+    // claims of 4096 workgroups alone took 60 us a launch: workgroups claim
+    // from one of kShards counters on lines of their own, counter r handing
+    // out the units G + r, G + r + kShards, ...
+    uint32_t unit = blockIdx.x;
+    if (unit >= units) return;
+    // The box is cleared once here; afterwards every flush returns the nodes
+    // it reads to zero, so each component and tile starts from a clear box.
+    for (int q = threadIdx.x; q < bnodes; q += blockDim.x) acc[q] = 0ull;
+    for (bool first = true;; first = false) {
+        if (!first) {
+            if (units <= G) break;
+            lds_barrier();   // every thread has read unit_sh of the round before
+            if (threadIdx.x == 0) {
+                const uint32_t r = blockIdx.x % kShards;
+                unit_sh = (int64_t)G + r + (int64_t)kShards * atomicAdd(&work[kCursor(colour, r)], 1u);
+            }
+            lds_barrier();
+            if (unit_sh >= units) break;
+            unit = (uint32_t)unit_sh;
         }
-        lds_barrier();
-        const int64_t t = tile_sh;
-        if (t < 0) break;
+        const uint32_t slot = split ? unit / 3u : unit;
+        const int c_beg = split ? (int)(unit - 3u * slot) : 0, c_end = split ? c_beg + 1 : 3;
+        const int64_t t = active[abase + slot];
+        if (t >= g.ntiles) break;
         const uint32_t beg = off[t], end = off[t + 1];
         const int tx = (int)(t % g.ntile[0]);
         const int ty = (int)((t / g.ntile[0]) % g.ntile[1]);
@@ -518,7 +531,7 @@ k_spread_colour(const Grid *__restrict__ gp, int colour, const uint32_t *__restr
         // one component at a time: a third of the LDS per workgroup, so more
         // workgroups fit a compute unit and tiles can be larger
 #pragma unroll 1
-        for (int c = 0; c < 3; ++c) {
+        for (int c = c_beg; c < c_end; ++c) {
             lds_barrier();
             // The tile's largest finite |c_l F_l| (written with c_l F_l by the
             // build, or k_spread_coef) sets its scale: with |phi_k| <= 4 every
@@ -675,7 +688,6 @@ k_spread_colour(const Grid *__restrict__ gp, int colour, const uint32_t *__restr
                 flush_box<false, BX>(g, c, acc, bnodes, bx, by, b0x, b0y, b0z, nxc, nyc, nzc, inv_bx, inv_by, inv_bxy,
                                      qscale, f);
         }
-        lds_barrier();
     }
 }
 
@@ -756,11 +768,10 @@ static SpreadScratch ctx_scratch(Ctx &c)
 }
 
 template <bool SORTED, int NF, int BX>
-static hipError_t launch_tiles_bx(Ctx &c, const SpreadScratch &sc, const uint32_t *home, const float *phi, float *fx,
-                                  float *fy, float *fz, hipStream_t s, bool timed)
+static hipError_t launch_tiles_bx(Ctx &c, const SpreadScratch &sc, int64_t n, const uint32_t *home,
+                                  const float *phi, float *fx, float *fy, float *fz, hipStream_t s, bool timed)
 {
     const size_t lds = spread_lds_bytes(c);
-    const int persist = c.cu_count * c.spread_blocks_per_cu;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)k_spread_colour<SORTED, NF, BX>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -769,6 +780,9 @@ static hipError_t launch_tiles_bx(Ctx &c, const SpreadScratch &sc, const uint32_
     TimedLaunch tt(c, timed ? MLS_K_SPREAD_TILES : -1, s);
     for (int col = 0; col < 27; ++col) {
         if (c.colour_tiles[col] == 0) continue;
+        // at most one workgroup per (tile, component) pair
+        const int64_t most = 3 * std::min(c.colour_tiles[col], n);
+        const unsigned persist = (unsigned)std::min((int64_t)c.cu_count * c.spread_blocks_per_cu, most);
         hipLaunchKernelGGL((k_spread_colour<SORTED, NF, BX>), dim3(persist), dim3(c.spread_threads), lds, s, c.d_grid,
                            col, home, phi, sc.cf, sc.cf_stride, fx, fy, fz, sc.tile_off, sc.entries, sc.tile_active,
                            sc.work, NF ? c.coef_rows : nullptr, c.w, sc.tile_fmax, c.g.ntiles + 1, c.err);
@@ -790,17 +804,17 @@ static int box_row_template(const Ctx &c)
 }
 
 template <bool SORTED, int NF>
-static hipError_t launch_tiles(Ctx &c, const SpreadScratch &sc, const uint32_t *home, const float *phi, float *fx,
-                               float *fy, float *fz, hipStream_t s, bool timed = true)
+static hipError_t launch_tiles(Ctx &c, const SpreadScratch &sc, int64_t n, const uint32_t *home, const float *phi,
+                               float *fx, float *fy, float *fz, hipStream_t s, bool timed = true)
 {
     switch (box_row_template(c)) {
-    case 7: return launch_tiles_bx<SORTED, NF, 7>(c, sc, home, phi, fx, fy, fz, s, timed);
-    case 9: return launch_tiles_bx<SORTED, NF, 9>(c, sc, home, phi, fx, fy, fz, s, timed);
-    case 11: return launch_tiles_bx<SORTED, NF, 11>(c, sc, home, phi, fx, fy, fz, s, timed);
-    case 13: return launch_tiles_bx<SORTED, NF, 13>(c, sc, home, phi, fx, fy, fz, s, timed);
-    case 15: return launch_tiles_bx<SORTED, NF, 15>(c, sc, home, phi, fx, fy, fz, s, timed);
-    case 19: return launch_tiles_bx<SORTED, NF, 19>(c, sc, home, phi, fx, fy, fz, s, timed);
-    default: return launch_tiles_bx<SORTED, NF, 0>(c, sc, home, phi, fx, fy, fz, s, timed);
+    case 7: return launch_tiles_bx<SORTED, NF, 7>(c, sc, n, home, phi, fx, fy, fz, s, timed);
+    case 9: return launch_tiles_bx<SORTED, NF, 9>(c, sc, n, home, phi, fx, fy, fz, s, timed);
+    case 11: return launch_tiles_bx<SORTED, NF, 11>(c, sc, n, home, phi, fx, fy, fz, s, timed);
+    case 13: return launch_tiles_bx<SORTED, NF, 13>(c, sc, n, home, phi, fx, fy, fz, s, timed);
+    case 15: return launch_tiles_bx<SORTED, NF, 15>(c, sc, n, home, phi, fx, fy, fz, s, timed);
+    case 19: return launch_tiles_bx<SORTED, NF, 19>(c, sc, n, home, phi, fx, fy, fz, s, timed);
+    default: return launch_tiles_bx<SORTED, NF, 0>(c, sc, n, home, phi, fx, fy, fz, s, timed);
     }
 }
 
@@ -845,7 +859,7 @@ static hipError_t launch_spread_with(Ctx &c, const SpreadScratch &sc, int64_t n,
                            c.d_grid, n, home, phi, area, Fx, Fy, Fz, sc.cf, sc.cf_stride, sc.marker_tile,
                            sc.tile_fmax, nt + 1);
     }
-    return launch_tiles<false, 0>(c, sc, home, phi, fx, fy, fz, s, timed);
+    return launch_tiles<false, 0>(c, sc, n, home, phi, fx, fy, fz, s, timed);
 }
 
 hipError_t launch_spread(Ctx &c, int64_t n, const uint32_t *home, const float *phi,
@@ -885,14 +899,14 @@ hipError_t launch_spread_sorted(Ctx &c, int64_t n, const uint32_t *home, const f
         TimedLaunch tb(c, MLS_K_SPREAD_BIN, s);
         // colour list sizes and tile cursors start at zero on every call (the
         // call may follow another spreading of the same sort)
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBlock), 0, s, c.work, (int64_t)64);
+        hipLaunchKernelGGL(k_zero_u32, dim3(kWorkWords / kBlock + 1), dim3(kBlock), 0, s, c.work, (int64_t)kWorkWords);
         hipLaunchKernelGGL(k_active_tiles, dim3((unsigned)((nt + kActiveChunk - 1) / kActiveChunk)), dim3(kBlock), 0,
                            s, c.d_grid, c.tile_off, c.tile_active, c.work);
     }
     const SpreadScratch sc = ctx_scratch(c);
-    if (c.step_nf == 7) return launch_tiles<true, 7>(c, sc, home, phi, fx, fy, fz, s);
-    if (c.step_nf == 13) return launch_tiles<true, 13>(c, sc, home, phi, fx, fy, fz, s);
-    return launch_tiles<true, 0>(c, sc, home, phi, fx, fy, fz, s);
+    if (c.step_nf == 7) return launch_tiles<true, 7>(c, sc, n, home, phi, fx, fy, fz, s);
+    if (c.step_nf == 13) return launch_tiles<true, 13>(c, sc, n, home, phi, fx, fy, fz, s);
+    return launch_tiles<true, 0>(c, sc, n, home, phi, fx, fy, fz, s);
 }
 
 
@@ -906,7 +920,7 @@ hipError_t launch_spread_sorted(Ctx &c, int64_t n, const uint32_t *home, const f
 // by noalloc_setup (called from mls_ctx_create, with that device current) and
 // kept in noalloc_ptr[]; every use on the host goes through that pointer.
 
-static __device__ __align__(256) unsigned char scratch[MLS_SPREAD_NOALLOC_BYTES];
+static __device__ __align__(256) unsigned char scratch[MLS_SPREAD_NOALLOC_BYTES + kWorkWords * 4];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -930,7 +944,8 @@ size_t carve(int64_t nt, int64_t n, unsigned char *base, SpreadScratch &sc)
     sc.tile_cursor = (uint32_t *)take((size_t)(nt + 1) * 4);
     sc.tile_active = (uint32_t *)take((size_t)nt * 4);
     sc.block_sums = (uint32_t *)take((size_t)(nb + 1) * 4);
-    sc.work = (uint32_t *)take(128 * 4);
+    take(128 * 4);   // part of the documented size; the list sizes and cursors lie behind it
+    sc.work = base ? (uint32_t *)(base + MLS_SPREAD_NOALLOC_BYTES) : nullptr;
     sc.tile_fmax = (uint32_t *)take((size_t)3 * (nt + 1) * 4);
     sc.marker_tile = (uint32_t *)take((size_t)n * 4);
     sc.entries = (uint32_t *)take((size_t)n * 4);
