@@ -234,12 +234,6 @@ k_build_interp(const Grid *__restrict__ gp, const Weight W, float tau, int64_t n
     wave_stats(st, routed, kmax);
 }
 
-// Zeroes n words (a kernel rather than a memset node, for graph capture).
-__global__ void k_clear_words(uint32_t *p, int64_t n)
-{
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
-}
-
 // The rows that the compact step build left to FP64: entry i of rq (after the
 // count) is row << 2 | component, row in tile order.  For each, the FP64
 // re-solve of the pair, its phi stored into the blocked rows, and the
@@ -745,8 +739,8 @@ hipError_t launch_build_interp(const Ctx &c, int64_t n, const float *x, const fl
                            nullptr, c.tile_fmax, c.g.ntiles + 1, c.err, c.stats);
         return hipGetLastError();
     }
-    // compact rows: clear the FP64 queue count, build, then finish the queued rows
-    hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, s, c.route_queue, (int64_t)1);
+    // compact rows: build (the binning cleared the FP64 queue's count), then
+    // finish the queued rows
     if (c.step_nf == 7)
         hipLaunchKernelGGL(k_build_interp<7>, grid, dim3(kBuildBlock), 0, s, c.d_grid, c.w, tau, n, c.entries, x, y,
                            z, home, phi, route, u, v, w, vb, area, 1.0f / dt, U, F, c.cf_rows, c.cf_stride,

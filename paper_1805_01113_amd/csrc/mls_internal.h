@@ -289,18 +289,20 @@ hipError_t launch_spread(Ctx &c, int64_t n, const uint32_t *home, const float *p
 int build_blocks(const Ctx &c, int64_t n);   // workgroups of a build launch over n markers
 // Bins the markers by spreading tile from their positions x, y, z; with jx
 // non-NULL the positions are first jittered (amplitude jitter, the step's
-// generator and device counter) into jx, jy, jz, and those are binned.
+// generator and device counter) into jx, jy, jz, and those are binned.  advance:
+// the device counter then moves on by one (a time step).
 hipError_t launch_sort_positions(Ctx &c, int64_t n, const float *x, const float *y, const float *z, hipStream_t s,
                                  float *jx = nullptr, float *jy = nullptr, float *jz = nullptr, float jitter = 0.0f,
-                                 uint64_t seed = 0);
+                                 uint64_t seed = 0, bool advance = false);
 int compact_nf(const Ctx &c);
 mls_status reserve_compact(mls_ctx *ctx, int64_t n);
 hipError_t launch_build_interp(const Ctx &c, int64_t n, const float *x, const float *y, const float *z,
                                uint32_t *home, float *phi, uint8_t *route, const float *u, const float *v,
                                const float *w, const float *vb, const float *area, float dt, float *U, float *F,
                                hipStream_t s);
+// again: the sort has been spread before (the autotuner times shapes on it).
 hipError_t launch_spread_sorted(Ctx &c, int64_t n, const uint32_t *home, const float *phi, float *fx, float *fy,
-                                float *fz, hipStream_t s);
+                                float *fz, hipStream_t s, bool again = false);
 // Dynamic LDS of a spreading tile workgroup: the int64 box of one component.
 size_t spread_lds_bytes(const Ctx &c);
 

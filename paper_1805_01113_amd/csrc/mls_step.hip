@@ -159,8 +159,10 @@ mls_status mls_step(mls_ctx *ctx, const mls_step_desc *desc, const mls_step_buff
             ~NfReset() { c.step_nf = 0; }
         } nf_reset{c};
         c.step_nf = compact ? compact_nf(c) : 0;
-        e = jitter ? launch_sort_positions(c, n, b->x0, b->y0, b->z0, s, b->x, b->y, b->z, desc->jitter, desc->seed)
-                   : launch_sort_positions(c, n, bx, by, bz, s);
+        // (the step counter advances once the jitter has read it)
+        e = jitter ? launch_sort_positions(c, n, b->x0, b->y0, b->z0, s, b->x, b->y, b->z, desc->jitter, desc->seed,
+                                           true)
+                   : launch_sort_positions(c, n, bx, by, bz, s, nullptr, nullptr, nullptr, 0.0f, 0, true);
         if (e != hipSuccess) return MLS_E_HIP;
         if (learned) {
             // the network (with its exact fallback) in tile order, fused with
@@ -181,7 +183,7 @@ mls_status mls_step(mls_ctx *ctx, const mls_step_desc *desc, const mls_step_buff
         e = launch_spread_sorted(c, n, b->home, b->phi, b->fx, b->fy, b->fz, s);
         if (e != hipSuccess) return MLS_E_HIP;
         c.step_sorted_n = n;
-        return launch_step_advance(c, s) == hipSuccess ? MLS_OK : MLS_E_HIP;
+        return MLS_OK;
     }
     st = mls_build(ctx, n, bx, by, bz, desc->method, b->home, b->phi, b->route, stream);
     if (st != MLS_OK) return st;

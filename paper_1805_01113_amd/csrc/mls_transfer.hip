@@ -162,17 +162,19 @@ k_bin(const Grid *__restrict__ gp, int64_t n, const uint32_t *__restrict__ home,
 // pass locates the markers and records each one's tile in tiles[]; the
 // filling pass reads it back.  With jitter (amp2 > 0) the counting pass reads
 // the rest positions x, y, z, jitters them (the time step's generator) and
-// stores the result in jx, jy, jz, which it then locates.
+// stores the result in jx, jy, jz, which it then locates.  The filling pass of
+// a time step, the counter's last reader behind it, advances the step counter
+// (step_ctr non-NULL).
 template <bool FILL>
 __global__ void __launch_bounds__(kBlock)
 k_bin_pos(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x, const float *__restrict__ y,
           const float *__restrict__ z, uint32_t *__restrict__ count, uint32_t *__restrict__ cursor,
           uint32_t *__restrict__ entries, uint32_t *__restrict__ tiles, float *__restrict__ jx,
-          float *__restrict__ jy, float *__restrict__ jz, float amp2, uint64_t seed,
-          const unsigned long long *__restrict__ step_ctr)
+          float *__restrict__ jy, float *__restrict__ jz, float amp2, uint64_t seed, unsigned long long *step_ctr)
 {
     const Grid &g = *gp;
     const uint64_t step = (!FILL && amp2 > 0.0f) ? *step_ctr : 0ull;
+    if (FILL && step_ctr && blockIdx.x == 0 && threadIdx.x == 0) *step_ctr += 1ull;
     const int lane = threadIdx.x & 63;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const float itx = g.ax[0].inv_tile, ity = g.ax[1].inv_tile, itz = g.ax[2].inv_tile;
@@ -210,15 +212,37 @@ k_bin_pos(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x, c
     }
 }
 
-__global__ void k_zero_u32(uint32_t *__restrict__ p, int64_t n)
+// Clears what a spreading call counts in: the n tile counts, the colour-list
+// sizes and claim cursors, and (compact step) the count of the FP64 queue.
+__global__ void k_clear(uint32_t *__restrict__ count, int64_t n, uint32_t *__restrict__ work,
+                        uint32_t *__restrict__ queue)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0 && queue) queue[0] = 0u;
+    for (int64_t i = i0; i < n + kWorkWords; i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < kWorkWords) work[i] = 0u;
+        else count[i - kWorkWords] = 0u;
+    }
 }
 
-// Exclusive scan of the tile counts: block partial sums, one workgroup scans
-// the partials, then each block scans its chunk.  off[ntiles] = total.
+// Zeroes n words (a kernel rather than a memset node, for graph capture).
+__global__ void k_clear_words(uint32_t *p, int64_t n)
+{
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
+}
+
+// Exclusive scan of the tile counts, off[ntiles] = total: every block scans
+// its chunk from the sum of the chunks before it (ScanFrom).  A launch costs
+// about 4.3 us however little it does, so the fewer the chunks, the fewer the
+// launches: up to kScanDirect chunks a block adds up the counts before its
+// chunk itself; up to kScanAdd chunks it adds up the chunks' sums (one launch
+// more); beyond that one workgroup scans the sums first (two more).  On one
+// sphere in 64^3 (one chunk) the step's binning went from seven launches to
+// four and its total from 30 to 18 us; a block of the last kernel reads at
+// most 64 KB of counts, or 16 KB of sums.
 constexpr int kScanChunk = 2048;   // elements per block (256 threads x 8)
+constexpr int kScanDirect = 8, kScanAdd = 4096;
+enum class ScanFrom { Counts, Sums, Scanned };
 
 __global__ void __launch_bounds__(kBlock) k_scan_partials(const uint32_t *__restrict__ count, int64_t nt,
                                                           uint32_t *__restrict__ partial)
@@ -250,57 +274,6 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(uint32_t *__restrict__ part
     }
 }
 
-// Also clears the per-tile force maxima tmax[3][tstride] of the scanned
-// tiles, ahead of the kernels that write c_l F_l.  Each thread scans 8
-// consecutive counts; the counts come in and the offsets go out through LDS
-// so that every global access of a wavefront is one contiguous run (8-element
-// strided stores leave partial lines that reach memory several times over).
-__global__ void __launch_bounds__(kBlock) k_scan_final(const uint32_t *__restrict__ count, int64_t nt,
-                                                       const uint32_t *__restrict__ partial,
-                                                       uint32_t *__restrict__ off, uint32_t *__restrict__ cursor,
-                                                       uint32_t *__restrict__ work, uint32_t *__restrict__ tmax,
-                                                       int64_t tstride)
-{
-    __shared__ uint32_t sh[4];
-    __shared__ uint32_t buf[kScanChunk];
-    const int64_t base = (int64_t)blockIdx.x * kScanChunk;
-    const int per = kScanChunk / kBlock;
-    for (int q = 0; q < per; ++q) {
-        const int64_t i = base + q * kBlock + threadIdx.x;
-        buf[q * kBlock + threadIdx.x] = i < nt ? count[i] : 0u;
-    }
-    __syncthreads();
-    uint32_t vals[kScanChunk / kBlock];
-    uint32_t s = 0;
-    for (int q = 0; q < per; ++q) {
-        vals[q] = buf[threadIdx.x * per + q];
-        s += vals[q];
-    }
-    uint32_t total;
-    uint32_t run = partial[blockIdx.x] + block_exclusive_scan(s, sh, total);
-    for (int q = 0; q < per; ++q) {
-        buf[threadIdx.x * per + q] = run;
-        run += vals[q];
-    }
-    // the owner of the last tile also writes off[nt] = total
-    const int64_t first = base + (int64_t)threadIdx.x * per;
-    if (first <= nt - 1 && nt - 1 < first + per) off[nt] = run;
-    __syncthreads();
-    for (int q = 0; q < per; ++q) {
-        const int64_t i = base + q * kBlock + threadIdx.x;
-        if (i < nt) {
-            const uint32_t o = buf[q * kBlock + threadIdx.x];
-            off[i] = o;
-            cursor[i] = o;
-            tmax[i] = 0u;
-            tmax[tstride + i] = 0u;
-            tmax[2 * tstride + i] = 0u;
-        }
-    }
-    if (blockIdx.x == 0)
-        for (int q = threadIdx.x; q < kWorkWords; q += kBlock) work[q] = 0u;   // colour list sizes and cursors
-}
-
 __device__ __forceinline__ int axis_colour(const Grid &g, int d, int t)
 {
     const int k = g.ncol[d];
@@ -315,41 +288,94 @@ __device__ __forceinline__ int64_t colour_end(const Grid &g, int col)
     return col + 1 < used ? g.colour_base[col + 1] : g.ntiles;
 }
 
-// Non-empty tiles listed per colour: work[col] counts them and
-// active[colour_base[col] + i] lists them.  A block gathers its 2048 tiles
-// per colour in LDS and takes its slots with one atomic per colour.
-constexpr int kActiveChunk = 2048;
+// Offsets of a chunk's tiles, and what else follows from its counts: the
+// per-tile force maxima tmax[3][tstride] are cleared, ahead of the kernels
+// that write c_l F_l, and the non-empty tiles are listed per colour
+// (work[col] counts them, active[colour_base[col] + i] lists them; a block
+// gathers its tiles in LDS and takes its slots with one atomic per colour).
+// Each thread scans 8 consecutive counts; the counts come in and the offsets
+// go out through LDS so that every global access of a wavefront is one
+// contiguous run (8-element strided stores leave partial lines that reach
+// memory several times over).
 __global__ void __launch_bounds__(kBlock)
-k_active_tiles(const Grid *__restrict__ gp, const uint32_t *__restrict__ off, uint32_t *__restrict__ active,
-               uint32_t *work)
+k_scan_final(const Grid *__restrict__ gp, const uint32_t *__restrict__ count, int64_t nt,
+             const uint32_t *__restrict__ partial, ScanFrom from, uint32_t *__restrict__ off,
+             uint32_t *__restrict__ cursor, uint32_t *__restrict__ work, uint32_t *__restrict__ active,
+             uint32_t *__restrict__ tmax, int64_t tstride)
 {
-    const Grid &g = *gp;
+    __shared__ uint32_t sh[4];
+    __shared__ uint32_t buf[kScanChunk];
     __shared__ uint32_t lcount[27], lbase[27];
+    const Grid &g = *gp;
+    const int64_t base = (int64_t)blockIdx.x * kScanChunk;
+    constexpr int per = kScanChunk / kBlock;
     if (threadIdx.x < 27) lcount[threadIdx.x] = 0u;
+    uint32_t before = 0;
+    if (from == ScanFrom::Scanned) {
+        before = partial[blockIdx.x];
+    } else {
+        uint32_t s = 0;
+        if (from == ScanFrom::Counts)
+            for (int64_t i = threadIdx.x; i < base; i += kBlock) s += count[i];
+        else
+            for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kBlock) s += partial[i];
+        block_exclusive_scan(s, sh, before);
+    }
+    for (int q = 0; q < per; ++q) {
+        const int64_t i = base + q * kBlock + threadIdx.x;
+        buf[q * kBlock + threadIdx.x] = i < nt ? count[i] : 0u;
+    }
     __syncthreads();
-    const int64_t t0 = (int64_t)blockIdx.x * kActiveChunk + (int64_t)threadIdx.x * (kActiveChunk / kBlock);
-    int col[kActiveChunk / kBlock];
-    uint32_t pos[kActiveChunk / kBlock];
+    const int64_t first = base + (int64_t)threadIdx.x * per;
+    uint32_t vals[per];
+    uint32_t s = 0;
 #pragma unroll
-    for (int q = 0; q < kActiveChunk / kBlock; ++q) {
-        const int64_t t = t0 + q;
+    for (int q = 0; q < per; ++q) {
+        vals[q] = buf[threadIdx.x * per + q];
+        s += vals[q];
+    }
+    int col[per];
+    uint32_t pos[per];
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        const int64_t t = first + q;
         col[q] = -1;
-        if (t < g.ntiles && off[t + 1] > off[t]) {
-            const int tx = (int)(t % g.ntile[0]);
-            const int ty = (int)((t / g.ntile[0]) % g.ntile[1]);
-            const int tz = (int)(t / ((int64_t)g.ntile[0] * g.ntile[1]));
+        if (vals[q] && t < g.ntiles) {
+            const uint32_t tu = (uint32_t)t, nx = (uint32_t)g.ntile[0], ny = (uint32_t)g.ntile[1];
+            const uint32_t row = tu / nx;
+            const int tx = (int)(tu - row * nx), ty = (int)(row % ny), tz = (int)(row / ny);
             col[q] = axis_colour(g, 0, tx) + g.ncol[0] * (axis_colour(g, 1, ty) + g.ncol[1] * axis_colour(g, 2, tz));
             pos[q] = atomicAdd(&lcount[col[q]], 1u);
         }
     }
-    __syncthreads();
-    if (threadIdx.x < 27) lbase[threadIdx.x] = lcount[threadIdx.x] ? atomicAdd(&work[threadIdx.x], lcount[threadIdx.x]) : 0u;
-    __syncthreads();
+    uint32_t total;
+    uint32_t run = before + block_exclusive_scan(s, sh, total);
 #pragma unroll
-    for (int q = 0; q < kActiveChunk / kBlock; ++q)
+    for (int q = 0; q < per; ++q) {
+        buf[threadIdx.x * per + q] = run;
+        run += vals[q];
+    }
+    // the owner of the last tile also writes off[nt] = total
+    if (first <= nt - 1 && nt - 1 < first + per) off[nt] = run;
+    if (threadIdx.x < 27)
+        lbase[threadIdx.x] = lcount[threadIdx.x] ? atomicAdd(&work[threadIdx.x], lcount[threadIdx.x]) : 0u;
+    __syncthreads();
+    for (int q = 0; q < per; ++q) {
+        const int64_t i = base + q * kBlock + threadIdx.x;
+        if (i < nt) {
+            const uint32_t o = buf[q * kBlock + threadIdx.x];
+            off[i] = o;
+            cursor[i] = o;
+            tmax[i] = 0u;
+            tmax[tstride + i] = 0u;
+            tmax[2 * tstride + i] = 0u;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < per; ++q)
         if (col[q] >= 0) {
             const int64_t slot = g.colour_base[col[q]] + lbase[col[q]] + pos[q];
-            if (slot < colour_end(g, col[q])) active[slot] = (uint32_t)(t0 + q);
+            if (slot < colour_end(g, col[q])) active[slot] = (uint32_t)(first + q);
         }
 }
 
@@ -830,6 +856,32 @@ hipError_t launch_interp(const Ctx &c, int64_t n, const uint32_t *home, const fl
     return hipGetLastError();
 }
 
+// Clears the nt tile counts and the colour lists of a call (and the count of
+// the FP64 queue, if given).
+static void launch_clear(const Ctx &c, const SpreadScratch &sc, int64_t nt, uint32_t *queue, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_clear, dim3(grid_for(nt + kWorkWords, c.cu_count)), dim3(kBlock), 0, s, sc.tile_count, nt,
+                       sc.work, queue);
+}
+
+// Offsets of nt tiles from their counts, with the colour lists (k_scan_final).
+static void launch_scan(const Ctx &c, const SpreadScratch &sc, int64_t nt, hipStream_t s)
+{
+    const int64_t nb = (nt + kScanChunk - 1) / kScanChunk;
+    ScanFrom from = ScanFrom::Counts;
+    if (nb > kScanDirect) {
+        hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)nb), dim3(kBlock), 0, s, sc.tile_count, nt, sc.block_sums);
+        from = ScanFrom::Sums;
+    }
+    if (nb > kScanAdd) {
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, sc.block_sums, nb);
+        from = ScanFrom::Scanned;
+    }
+    hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nb), dim3(kBlock), 0, s, c.d_grid, sc.tile_count, nt,
+                       sc.block_sums, from, sc.tile_off, sc.tile_cursor, sc.work, sc.tile_active, sc.tile_fmax,
+                       c.g.ntiles + 1);
+}
+
 // The standalone spreading on the buffers sc: binning from the homes, c_l F_l
 // and the per-tile maxima by marker, then the coloured tile launches.  timed:
 // per-kernel timing marks (they may create HIP events).
@@ -839,22 +891,15 @@ static hipError_t launch_spread_with(Ctx &c, const SpreadScratch &sc, int64_t n,
 {
     if (n == 0) return hipSuccess;
     const int64_t nt = c.g.ntiles;
-    const int64_t nb = (nt + kScanChunk - 1) / kScanChunk;
     {
         TimedLaunch tb(c, timed ? MLS_K_SPREAD_BIN : -1, s);
-        hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(nt, c.cu_count)), dim3(kBlock), 0, s, sc.tile_count, nt);
+        launch_clear(c, sc, nt, nullptr, s);
         const int gbin = grid_for(n, c.cu_count);
         hipLaunchKernelGGL(k_bin<false>, dim3(gbin), dim3(kBlock), 0, s, c.d_grid, n, home, sc.tile_count,
                            sc.tile_cursor, sc.entries, sc.marker_tile, c.err);
-        hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)nb), dim3(kBlock), 0, s, sc.tile_count, nt,
-                           sc.block_sums);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, sc.block_sums, nb);
-        hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nb), dim3(kBlock), 0, s, sc.tile_count, nt, sc.block_sums,
-                           sc.tile_off, sc.tile_cursor, sc.work, sc.tile_fmax, nt + 1);
-        hipLaunchKernelGGL(k_bin<true>, dim3(grid_for(n, c.cu_count)), dim3(kBlock), 0, s, c.d_grid, n, home,
-                           sc.tile_count, sc.tile_cursor, sc.entries, sc.marker_tile, c.err);
-        hipLaunchKernelGGL(k_active_tiles, dim3((unsigned)((nt + kActiveChunk - 1) / kActiveChunk)), dim3(kBlock), 0,
-                           s, c.d_grid, sc.tile_off, sc.tile_active, sc.work);
+        launch_scan(c, sc, nt, s);
+        hipLaunchKernelGGL(k_bin<true>, dim3(gbin), dim3(kBlock), 0, s, c.d_grid, n, home, sc.tile_count,
+                           sc.tile_cursor, sc.entries, sc.marker_tile, c.err);
         hipLaunchKernelGGL(k_spread_coef, dim3((unsigned)round_up8(grid_for(n, c.cu_count))), dim3(kBlock), 0, s,
                            c.d_grid, n, home, phi, area, Fx, Fy, Fz, sc.cf, sc.cf_stride, sc.marker_tile,
                            sc.tile_fmax, nt + 1);
@@ -870,40 +915,32 @@ hipError_t launch_spread(Ctx &c, int64_t n, const uint32_t *home, const float *p
 }
 
 hipError_t launch_sort_positions(Ctx &c, int64_t n, const float *x, const float *y, const float *z, hipStream_t s,
-                                 float *jx, float *jy, float *jz, float jitter, uint64_t seed)
+                                 float *jx, float *jy, float *jz, float jitter, uint64_t seed, bool advance)
 {
     const float amp2 = jx ? 2.0f * jitter : 0.0f;
     if (n == 0) return hipSuccess;
     const int64_t nt = c.g.ntiles + 1;   // tiles and the bucket of markers without a valid support
-    const int64_t nb = (nt + kScanChunk - 1) / kScanChunk;
+    const SpreadScratch sc = ctx_scratch(c);
     TimedLaunch tb(c, MLS_K_SPREAD_BIN, s);
-    hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(nt, c.cu_count)), dim3(kBlock), 0, s, c.tile_count, nt);
+    launch_clear(c, sc, nt, c.step_nf ? c.route_queue : nullptr, s);
     hipLaunchKernelGGL(k_bin_pos<false>, dim3(grid_for(n, c.cu_count)), dim3(kBlock), 0, s, c.d_grid, n, x, y, z,
                        c.tile_count, c.tile_cursor, c.entries, c.marker_tile, jx, jy, jz, amp2, seed, c.step_ctr);
-    hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)nb), dim3(kBlock), 0, s, c.tile_count, nt, c.block_sums);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, c.block_sums, nb);
-    hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nb), dim3(kBlock), 0, s, c.tile_count, nt, c.block_sums,
-                       c.tile_off, c.tile_cursor, c.work, c.tile_fmax, c.g.ntiles + 1);
+    launch_scan(c, sc, nt, s);
     hipLaunchKernelGGL(k_bin_pos<true>, dim3(grid_for(n, c.cu_count)), dim3(kBlock), 0, s, c.d_grid, n, x, y, z,
                        c.tile_count, c.tile_cursor, c.entries, c.marker_tile, nullptr, nullptr, nullptr, 0.0f,
-                       (uint64_t)0, c.step_ctr);
+                       (uint64_t)0, advance ? c.step_ctr : nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_spread_sorted(Ctx &c, int64_t n, const uint32_t *home, const float *phi, float *fx, float *fy,
-                                float *fz, hipStream_t s)
+                                float *fz, hipStream_t s, bool again)
 {
     if (n == 0) return hipSuccess;
-    const int64_t nt = c.g.ntiles;
-    {
-        TimedLaunch tb(c, MLS_K_SPREAD_BIN, s);
-        // colour list sizes and tile cursors start at zero on every call (the
-        // call may follow another spreading of the same sort)
-        hipLaunchKernelGGL(k_zero_u32, dim3(kWorkWords / kBlock + 1), dim3(kBlock), 0, s, c.work, (int64_t)kWorkWords);
-        hipLaunchKernelGGL(k_active_tiles, dim3((unsigned)((nt + kActiveChunk - 1) / kActiveChunk)), dim3(kBlock), 0,
-                           s, c.d_grid, c.tile_off, c.tile_active, c.work);
-    }
     const SpreadScratch sc = ctx_scratch(c);
+    // the sort clears the claim cursors; a further spreading of it clears them here
+    if (again)
+        hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(kBlock), 0, s, sc.work + kCursor(0, 0),
+                           (int64_t)(kWorkWords - kCursor(0, 0)));
     if (c.step_nf == 7) return launch_tiles<true, 7>(c, sc, n, home, phi, fx, fy, fz, s);
     if (c.step_nf == 13) return launch_tiles<true, 13>(c, sc, n, home, phi, fx, fy, fz, s);
     return launch_tiles<true, 0>(c, sc, n, home, phi, fx, fy, fz, s);

@@ -236,8 +236,8 @@ mls_status mls_autotune(mls_ctx *ctx, int32_t method, int32_t flags, const mls_s
     };
     auto spread = [&]() {
         if (exact)
-            return launch_spread_sorted(c, n, b->home, b->phi, b->fx, b->fy, b->fz, s) == hipSuccess ? MLS_OK
-                                                                                                     : MLS_E_HIP;
+            return launch_spread_sorted(c, n, b->home, b->phi, b->fx, b->fy, b->fz, s, true) == hipSuccess
+                       ? MLS_OK : MLS_E_HIP;
         return mls_spread(ctx, n, b->home, b->phi, b->area, F, F + n, F + 2 * n, b->fx, b->fy, b->fz, stream);
     };
     bool ok = true;
