@@ -113,30 +113,51 @@ mls_status mls::setup_tiles(Ctx &c, int want)
     // positions
     const int64_t nb = (nt + 1 + 2047) / 2048;
     uint32_t *tcount = nullptr, *toff = nullptr, *tcur = nullptr, *tact = nullptr, *bsum = nullptr,
-             *tmax = nullptr;
+             *tmax = nullptr, *tslot = nullptr;
     bool ok = hipMalloc((void **)&tcount, (nt + 1) * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc((void **)&toff, (nt + 2) * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc((void **)&tcur, (nt + 1) * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc((void **)&tact, nt * sizeof(uint32_t)) == hipSuccess &&
+              hipMalloc((void **)&tslot, nt * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc((void **)&bsum, (nb + 1) * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc((void **)&tmax, 3 * (nt + 1) * sizeof(uint32_t)) == hipSuccess;
     ok = ok && hipDeviceSynchronize() == hipSuccess &&
          hipMemcpy(c.d_grid, &g, sizeof(Grid), hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) {
         hipFree(tcount); hipFree(toff); hipFree(tcur); hipFree(tact); hipFree(bsum); hipFree(tmax);
+        hipFree(tslot);
         hipMemcpy(c.d_grid, &c.g, sizeof(Grid), hipMemcpyHostToDevice);
         return MLS_E_NOMEM;
     }
     hipFree(c.tile_count); hipFree(c.tile_off); hipFree(c.tile_cursor);
-    hipFree(c.tile_active); hipFree(c.block_sums); hipFree(c.tile_fmax);
+    hipFree(c.tile_active); hipFree(c.block_sums); hipFree(c.tile_fmax); hipFree(c.tile_slot);
     c.tile_count = tcount; c.tile_off = toff; c.tile_cursor = tcur; c.tile_active = tact; c.block_sums = bsum;
-    c.tile_fmax = tmax;
+    c.tile_fmax = tmax; c.tile_slot = tslot;
     c.g = g;
     ++c.scratch_gen;
     for (int k = 0; k < 27; ++k) c.colour_tiles[k] = colour_tiles[k];
     c.spread_blocks_per_cu = std::max(1, std::min(c.spread_blocks_per_cu_req, (int)((160 * 1024) / (lds + 512))));
     c.opts.spread_tile = want;
+    reserve_stage(c);   // without it, spreading takes one launch per colour
     return MLS_OK;
+}
+
+bool mls::reserve_stage(Ctx &c)
+{
+    const int64_t per = stage_floats(c, 1), tiles = std::min(c.g.ntiles, c.cap_markers);
+    const int64_t need = per * std::min(tiles, kStageBytes / (int64_t)sizeof(float) / per);
+    if (need <= c.stage_floats) return true;
+    hipFree(c.stage);
+    c.stage = nullptr;
+    c.stage_floats = 0;
+    ++c.scratch_gen;
+    if (hipMalloc((void **)&c.stage, (size_t)need * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        c.stage = nullptr;
+        return false;
+    }
+    c.stage_floats = need;
+    return true;
 }
 
 namespace mls {
@@ -376,6 +397,8 @@ void mls_ctx_destroy(mls_ctx *ctx)
     hipFree(c.tile_active);
     hipFree(c.block_sums);
     hipFree(c.tile_fmax);
+    hipFree(c.tile_slot);
+    hipFree(c.stage);
     hipFree(c.entries);
     hipFree(c.cf_rows);
     hipFree(c.marker_tile);
@@ -419,6 +442,7 @@ mls_status mls_reserve(mls_ctx *ctx, int64_t n)
     }
     c.cap_markers = n;
     c.cf_stride = stride;
+    reserve_stage(c);   // without it, spreading takes one launch per colour
     return MLS_OK;
 }
 

@@ -32,6 +32,9 @@ constexpr uint32_t kMaskI = (1u << kPackI) - 1, kMaskJ = (1u << kPackJ) - 1;
 // kShards claim cursors per colour, each on a 128-byte line of its own.
 constexpr int kShards = 8;
 constexpr __host__ __device__ int kCursor(int colour, int shard) { return 64 + (colour * kShards + shard) * 32; }
+// Staging buffer of the spreading in two launches: the boxes of 4200 tiles of
+// eight cells.  Up to that many tiles it is faster than one launch per colour.
+constexpr int64_t kStageBytes = 64ll << 20;
 constexpr int kWorkWords = 64 + 27 * kShards * 32;
 
 // One axis of the Eulerian grid as the device sees it.
@@ -174,6 +177,9 @@ struct Ctx {
     uint32_t *tile_off = nullptr;      // ntiles + 2
     uint32_t *tile_cursor = nullptr;   // ntiles + 1
     uint32_t *tile_active = nullptr;   // ntiles: non-empty tiles, grouped by colour
+    uint32_t *tile_slot = nullptr;     // ntiles: place of a non-empty tile in its colour's list
+    float *stage = nullptr;            // staged tile boxes of a spreading in two launches (at most kStageBytes)
+    int64_t stage_floats = 0;
     uint32_t *block_sums = nullptr;    // scan partials
     uint32_t *entries = nullptr;       // cap_markers: markers sorted by tile
     float *cf_rows = nullptr;          // [3][cf_stride]: c_l F_l (eq. 8) by row (step, tile order) or by marker
@@ -303,6 +309,7 @@ hipError_t launch_build_interp(const Ctx &c, int64_t n, const float *x, const fl
 // again: the sort has been spread before (the autotuner times shapes on it).
 hipError_t launch_spread_sorted(Ctx &c, int64_t n, const uint32_t *home, const float *phi, float *fx, float *fy,
                                 float *fz, hipStream_t s, bool again = false);
+int64_t stage_floats(const Ctx &c, int64_t tiles);
 // Dynamic LDS of a spreading tile workgroup: the int64 box of one component.
 size_t spread_lds_bytes(const Ctx &c);
 
@@ -322,6 +329,10 @@ hipError_t launch_force(const Ctx &c, int64_t n, const float *vb, const float *U
 hipError_t launch_step_advance(const Ctx &c, hipStream_t s);
 
 FastTables fast_tables(const Ctx &c);
+
+// Staging buffer for any spreading of up to cap_markers markers that can use
+// it; false if it cannot be allocated.
+bool reserve_stage(Ctx &c);
 
 // (Re)cut the spreading tiles for edge `want` (see mls_ctx_create).
 mls_status setup_tiles(Ctx &c, int want);

@@ -1,6 +1,7 @@
 """GPU: the tile scan of the spreading over its three ways of finding a
 chunk's offset (from the counts of the chunks before it, from their sums, from
-their scanned sums), at the sizes where one gives way to the next.
+their scanned sums), at the sizes where one gives way to the next, and the
+spreading in two launches against one launch per colour.
 
 A chunk is 2048 tiles; up to 8 chunks a block adds up counts, up to 4096 it
 adds up sums.  A time step scans one bucket more than a stand-alone call, so
@@ -86,3 +87,37 @@ def test_scan_of_the_largest_tilings(torch_cuda):
     for p, q in zip(*out):
         top = float(p.abs().max())
         assert top > 0.0 and float((p - q).abs().max()) <= 1e-6 * top
+
+
+@pytest.mark.parametrize("n,wall,tile,count", [
+    ((16, 24, 32), False, 8, 700),       # one whole axis, three tiles (odd), four tiles
+    ((24, 24, 24), False, 12, 1),        # two tiles an axis: both neighbours are the same tile
+    ((20, 35, 18), False, 5, 65),        # tiles of 5, 5 or 7, and 9 or 6 cells
+    ((32, 40, 21), True, 8, 900),        # a last tile cut short by the wall
+    ((48, 16, 64), True, 16, 4000),      # the largest boxes
+    ((64, 64, 64), False, 4, 20000),     # many small, crowded tiles
+])
+def test_two_launches_equal_colour_launches(torch_cuda, n, wall, tile, count):
+    """mls_spread takes two launches through its staging buffer where the boxes
+    fit it, mls_spread_noalloc always one launch per colour: the forcing, added
+    to fields that are not zero, is the same bit for bit."""
+    from paper_1805_01113_amd import mls
+    torch = torch_cuda
+    g = W.GridSpec([W.uniform_faces(n[d], n[d] / n[0]) for d in range(3)], [True, True, not wall])
+    pos, area, force = _markers(n, count, 13)
+    if wall:
+        lo, hi = 1.5 / n[0], (n[2] - 1.5) / n[0]
+        pos[2] = np.clip(pos[2], np.float32(lo), np.float32(hi))
+    ctx = mls.Context(g.faces, g.periodic, spread_tile=tile)
+    x, y, z, a = [torch.from_numpy(v).cuda() for v in (*pos, area)]
+    F = torch.from_numpy(force).cuda()
+    home, phi, _ = ctx.build(x, y, z)
+    start = [torch.randn(g.shape(c), device="cuda", generator=torch.Generator("cuda").manual_seed(c))
+             for c in range(3)]
+    one, two = [v.clone() for v in start], [v.clone() for v in start]
+    ctx.spread_noalloc(home, phi, a, F, one)
+    ctx.spread(home, phi, a, F, two)
+    ctx.sync()
+    for c in range(3):
+        assert torch.equal(one[c], two[c])
+        assert not torch.equal(one[c], start[c])
