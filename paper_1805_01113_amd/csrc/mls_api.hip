@@ -780,7 +780,8 @@ mls_status mls_features(mls_ctx *ctx, int64_t n, const float *x, const float *y,
     return MLS_OK;
 }
 
-static mls_status mlp_batch_check(mls_ctx *ctx, int64_t m, const float *feat, int64_t rows, const int64_t *idx)
+static mls_status mlp_batch_check(mls_ctx *ctx, int64_t m, const float *feat, int64_t rows, const int64_t *idx,
+                                  bool train)
 {
     Ctx &c = ctx->c;
     if (!c.mlp.loaded) return fail(ctx, MLS_E_ARG, "no network loaded");
@@ -788,7 +789,7 @@ static mls_status mlp_batch_check(mls_ctx *ctx, int64_t m, const float *feat, in
     if (m > 0 && !feat) return fail(ctx, MLS_E_ARG, "null array");
     if (rows < 0 || (!idx && m > rows)) return fail(ctx, MLS_E_ARG, "batch of %lld rows from %lld", (long long)m,
                                                     (long long)rows);
-    hipError_t e = mlp_reserve(c, m);
+    hipError_t e = train ? mlp_reserve(c, m) : hipSuccess;   // the forward pass keeps everything in registers
     if (e != hipSuccess) return hip_fail(ctx, e, "training scratch");
     return MLS_OK;
 }
@@ -797,7 +798,7 @@ mls_status mls_mlp_forward(mls_ctx *ctx, int64_t m, const float *feat, int64_t r
                            void *stream)
 {
     if (!ctx) return MLS_E_ARG;
-    mls_status st = mlp_batch_check(ctx, m, feat, rows, idx);
+    mls_status st = mlp_batch_check(ctx, m, feat, rows, idx, false);
     if (st != MLS_OK) return st;
     if (m > 0 && !out) return fail(ctx, MLS_E_ARG, "null array");
     hipError_t e = mlp_forward_batch(ctx->c, m, feat, rows, idx, out, static_cast<hipStream_t>(stream));
@@ -809,7 +810,7 @@ mls_status mls_mlp_grad(mls_ctx *ctx, int64_t m, const float *feat, const float 
                         const int64_t *idx, float mu, float *grad, float *loss, void *stream)
 {
     if (!ctx) return MLS_E_ARG;
-    mls_status st = mlp_batch_check(ctx, m, feat, rows, idx);
+    mls_status st = mlp_batch_check(ctx, m, feat, rows, idx, true);
     if (st != MLS_OK) return st;
     if (m < 1 || !target || !grad || !loss) return fail(ctx, MLS_E_ARG, "null array or empty batch");
     if (!(mu >= 0.0f) || !std::isfinite(mu)) return fail(ctx, MLS_E_ARG, "bad mu");
@@ -822,15 +823,14 @@ mls_status mls_mlp_train_step(mls_ctx *ctx, int64_t m, const float *feat, const 
                               const int64_t *idx, float mu, float lr, float *loss, void *stream)
 {
     if (!ctx) return MLS_E_ARG;
-    mls_status st = mlp_batch_check(ctx, m, feat, rows, idx);
+    mls_status st = mlp_batch_check(ctx, m, feat, rows, idx, true);
     if (st != MLS_OK) return st;
     if (m < 1 || !target) return fail(ctx, MLS_E_ARG, "null array or empty batch");
     if (!(mu >= 0.0f) || !std::isfinite(mu) || !(lr >= 0.0f) || !std::isfinite(lr))
         return fail(ctx, MLS_E_ARG, "bad mu or learning rate");
     Ctx &c = ctx->c;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = mlp_grad_batch(c, m, feat, target, rows, idx, mu, c.mlp.grad, loss ? loss : c.mlp.loss, s);
-    if (e == hipSuccess) e = mlp_adam(c, lr, s);
+    hipError_t e = mlp_train_batch(c, m, feat, target, rows, idx, mu, lr, loss ? loss : c.mlp.loss, s);
     if (e != hipSuccess) return hip_fail(ctx, e, "training step");
     return MLS_OK;
 }

@@ -139,13 +139,13 @@ static_assert(kMlpImageTableOffset % 16 == 0, "GELU table rows are 16-byte align
 struct Mlp {
     bool loaded = false;
     float *params = nullptr;   // kMlpParams (FP32 master copy)
-    float *grad = nullptr;     // kMlpParams
     float *m1 = nullptr, *m2 = nullptr;   // Adam moments
     float *norm = nullptr;     // 12
     void *image = nullptr;     // kMlpImageBytes
+    void *train_image = nullptr;   // the weights as operands of the training kernels
     float *loss = nullptr;     // 1 (device)
     float h_norm[12] = {};
-    int64_t version = 0, image_version = -1;
+    int64_t version = 0, image_version = -1, train_version = -1;
     int64_t adam_step = 0;
     float *scratch = nullptr;  // training activations
     int64_t cap_batch = 0;
@@ -348,7 +348,8 @@ hipError_t mlp_forward_batch(Ctx &c, int64_t m, const float *feat, int64_t rows,
                              hipStream_t s);
 hipError_t mlp_grad_batch(Ctx &c, int64_t m, const float *feat, const float *target, int64_t rows,
                           const int64_t *idx, float mu, float *grad, float *loss, hipStream_t s);
-hipError_t mlp_adam(Ctx &c, float lr, hipStream_t s);
+hipError_t mlp_train_batch(Ctx &c, int64_t m, const float *feat, const float *target, int64_t rows,
+                           const int64_t *idx, float mu, float lr, float *loss, hipStream_t s);
 
 }  // namespace mls
 

@@ -10,11 +10,13 @@
 // hi*hi + hi*lo + lo*hi is accumulated in FP32 (the dropped lo*lo term and
 // the rounding of lo leave a relative error near 2^-17 per product).
 //
-// Training: a general matrix-product kernel (optionally split along k, with
-// the chunks summed in a fixed order), elementwise GELU / loss kernels and
-// Adam; every reduction has a fixed order, so a training run is reproducible.
-// Bias gradients come out of the weight-gradient products by appending a row
-// of ones to the activations (b follows W in the parameter vector).
+// Training: a step is three launches.  k_mlp_pass takes 16 samples per
+// workgroup through the forward pass, the loss and the backward pass with all
+// activations in registers, and leaves the layers' inputs and output gradients
+// in memory; k_mlp_wgrad forms the weight gradients from them in chunks of the
+// batch; k_mlp_update sums the chunks in order, applies Adam and refreshes the
+// packed operands.  Every reduction has a fixed order, so a training run is
+// reproducible.
 //
 // Inference (mls_build with MLS_LEARNED): one wavefront per (64-marker block,
 // component) computes the features, evaluates the network for 32 markers at a
@@ -38,7 +40,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBlock = 256;
 constexpr int kLearnBlock = 512;        // 8 wavefronts share one copy of the network in LDS
-constexpr int kSplitChunk = 2048;       // k-chunk of the weight-gradient products
 
 // ---- activation ------------------------------------------------------------
 // The standard normal tail Q(x) = 1 - Phi(x) = erfc(x / sqrt 2) / 2 for x >= 0
@@ -64,12 +65,15 @@ __device__ __forceinline__ float gelu(float z)
     return z * (z >= 0.0f ? 1.0f - q : q);
 }
 
-// gelu'(z) = Phi(z) + z phi(z), phi(z) = exp(-z^2/2) / sqrt(2 pi)
-__device__ __forceinline__ float gelu_grad(float z)
+// The same with its derivative gelu'(z) = Phi(z) + z phi(z), phi(z) =
+// exp(-z^2/2) / sqrt(2 pi).
+__device__ __forceinline__ float gelu(float z, float &dz)
 {
     float ez;
     const float q = normal_tail(fabsf(z), ez);
-    return (z >= 0.0f ? 1.0f - q : q) + z * ez * 0.39894228040143268f;
+    const float cdf = z >= 0.0f ? 1.0f - q : q;
+    dz = cdf + z * ez * 0.39894228040143268f;
+    return z * cdf;
 }
 
 // gelu(z) = max(z, 0) - |z| Q(|z|) from the cubic table of the network image
@@ -100,67 +104,7 @@ __device__ __forceinline__ f32x16 mfma3(bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 
     return c;
 }
 
-// ---- general matrix product (training) --------------------------------------
-// C(m, n) = sum_{k in chunk} A(m, k) B(k, n) with strided FP32 operands
-// A(m, k) = A[m sam + k sak] for m < Ma and A(Ma, k) = 1 if ones_row (so M =
-// Ma + ones_row), B(k, n) = B[k sbk + n sbn]; chunk blockIdx.y covers
-// k in [y kc, min(K, (y + 1) kc)) and writes C + y cchunk, C(m, n) at
-// C[m scm + n scn].  One wavefront per 32 x 32 tile of C on
-// v_mfma_f32_32x32x16_bf16: operand lane l holds row (A) / column (B) l % 32
-// and k = k0 + 8 (l / 32) + i, i < 8; result register j of lane l is row
-// 8 (j / 4) + 4 (l / 32) + j % 4, column l % 32.
-__global__ void __launch_bounds__(kBlock)
-k_gemm(int Ma, int ones_row, int N, int K, int kc, const float *__restrict__ A, int64_t sam, int64_t sak,
-       const float *__restrict__ B, int64_t sbk, int64_t sbn, float *__restrict__ C, int64_t scm, int64_t scn,
-       int64_t cchunk)
-{
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 31, h = lane >> 5;
-    const int M = Ma + ones_row;
-    const int tiles_n = (N + 31) / 32;
-    const int tiles = ((M + 31) / 32) * tiles_n;
-    const int wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (wave >= tiles) return;
-    const int tm = wave / tiles_n, tn = wave % tiles_n;
-    const int m = tm * 32 + r, n = tn * 32 + r;
-    const int kbeg = blockIdx.y * kc;
-    const int kend = min(K, kbeg + kc);
-    f32x16 acc = {};
-    for (int k0 = kbeg; k0 < kend; k0 += 16) {
-        bf16x8 ahi, alo, bhi, blo;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int k = k0 + 8 * h + i;
-            const bool kin = k < kend;
-            float av = 0.0f;
-            if (kin && m < Ma) av = A[(int64_t)m * sam + (int64_t)k * sak];
-            else if (kin && m == Ma && ones_row) av = 1.0f;
-            const float bv = (kin && n < N) ? B[(int64_t)k * sbk + (int64_t)n * sbn] : 0.0f;
-            __bf16 p, q;
-            split_bf16(av, p, q);
-            ahi[i] = p; alo[i] = q;
-            split_bf16(bv, p, q);
-            bhi[i] = p; blo[i] = q;
-        }
-        acc = mfma3(ahi, alo, bhi, blo, acc);
-    }
-    float *Cc = C + (int64_t)blockIdx.y * cchunk;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int row = tm * 32 + 8 * (j / 4) + 4 * h + (j % 4);
-        if (row < M && n < N) Cc[(int64_t)row * scm + (int64_t)n * scn] = acc[j];
-    }
-}
-
-// out[i] = sum_{c < chunks} part[c * count + i], chunks in order
-__global__ void k_sum_chunks(int64_t count, int chunks, const float *__restrict__ part, float *__restrict__ out)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (int c = 0; c < chunks; ++c) s += part[(int64_t)c * count + i];
-        out[i] = s;
-    }
-}
+// ---- training -----------------------------------------------------------------
 
 // Row of batch entry b: idx[b] if idx is given, else b.  An index outside
 // [0, rows) raises MLS_E_ARG on the device and reads row 0 instead.
@@ -173,36 +117,6 @@ __device__ __forceinline__ int64_t batch_row(const int64_t *idx, int64_t b, int6
         return 0;
     }
     return r;
-}
-
-// U[m] = (feat[row(m)] - shift) * scale
-__global__ void k_normalize(int64_t M, const float *__restrict__ feat, int64_t rows, const int64_t *__restrict__ idx,
-                            const float *__restrict__ norm, float *__restrict__ U, ErrWord *err)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < M * 6; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t m = i / 6;
-        const int f = (int)(i - m * 6);
-        const int64_t row = batch_row(idx, m, rows, err);
-        U[i] = (feat[row * 6 + f] - norm[f]) * norm[6 + f];
-    }
-}
-
-// Z[m][n] += bias[n]; H = gelu(Z) unless H is null
-__global__ void k_bias_act(int64_t M, int N, float *__restrict__ Z, float *__restrict__ H,
-                           const float *__restrict__ bias)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < M * N; i += (int64_t)gridDim.x * blockDim.x) {
-        const float zv = Z[i] + bias[i % N];
-        Z[i] = zv;
-        if (H) H[i] = gelu(zv);
-    }
-}
-
-// D = D * gelu'(Z) (in place)
-__global__ void k_gelu_bwd(int64_t count, float *__restrict__ D, const float *__restrict__ Z)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-        D[i] *= gelu_grad(Z[i]);
 }
 
 // Offsets of the three support nodes from the marker along each axis in
@@ -220,66 +134,443 @@ __device__ __forceinline__ void node_offsets(const float *f, float s[3][3])
     }
 }
 
-// Loss L = mean_{b,k} (y - t)^2 + mu mean_b [(sum_k y - 1)^2 + sum_d (sum_k y s_dk)^2]
-// and dL/dY; one thread per sample, per-block partial sums of L.
-__global__ void __launch_bounds__(kBlock)
-k_loss_grad(int64_t M, const float *__restrict__ Y, const float *__restrict__ T, const float *__restrict__ feat,
-            int64_t rows, const int64_t *__restrict__ idx, float mu, float *__restrict__ dY, float *__restrict__ partial,
-            ErrWord *err)
+// Operands of the training kernels: every weight matrix as the A operands of
+// v_mfma_f32_16x16x32_bf16 (lane l: output row l % 16, eight inputs), split
+// into a high and a low BF16 part.  Slot s holds
+//   0 + T        W1^T, rows 16 T .. (hidden units), inputs the 6 features
+//   8 + 4 T + kb W2^T, rows 16 T .., inputs of k block kb
+//   40 + 4 T + kb W3^T, rows 16 T .. (27 outputs)
+//   48 + T       W3, rows 16 T .. (hidden units), inputs the 27 outputs
+//   56 + 4 T + kb W2, rows 16 T .. (first-layer units), inputs of block kb
+// A result tile leaves rows 4 (l / 16) + j of column l % 16 in registers j < 4,
+// so two tiles in a row are the B operand of the next product if its k slot
+// (l / 16, i) stands for input 32 kb + 16 (i / 4) + 4 (l / 16) + i % 4: the
+// products chain through registers without a shuffle.
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+constexpr int kTrainSlots = 88;
+constexpr size_t kTrainImageBytes = (size_t)kTrainSlots * 2 * 64 * 16;
+
+// Writes parameter p (value v) into its one or two places of the image.
+__device__ __forceinline__ void pack_train(__bf16 *img, int p, float v)
 {
-    __shared__ float red[kBlock / 64];
-    float acc = 0.0f;
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < M) {
-        const int64_t row = batch_row(idx, b, rows, err);
-        float s[3][3];
-        node_offsets(feat + row * 6, s);
-        const float *y = Y + b * kNe;
-        const float *t = T + row * kNe;
-        float sy = 0.0f, r1[3] = {0.0f, 0.0f, 0.0f}, se = 0.0f;
-        for (int k = 0; k < kNe; ++k) {
-            const float e = y[k] - t[k];
-            se += e * e;
-            sy += y[k];
-            r1[0] += y[k] * s[0][k % 3];
-            r1[1] += y[k] * s[1][(k / 3) % 3];
-            r1[2] += y[k] * s[2][k / 9];
+    __bf16 hi, lo;
+    split_bf16(v, hi, lo);
+    auto put = [&](int slot, int lane, int e) {
+        img[(((slot * 2) * 64) + lane) * 8 + e] = hi;
+        img[(((slot * 2 + 1) * 64) + lane) * 8 + e] = lo;
+    };
+    // k slot of input q within its block of 32
+    auto grp = [](int q) { return (q >> 2) & 3; };
+    auto elt = [](int q) { return ((q >> 4) & 1) * 4 + (q & 3); };
+    if (p < kOffB1) {
+        const int i = p / kMlpHidden, o = p % kMlpHidden;
+        put(o >> 4, o & 15, i);
+    } else if (p >= kOffW2 && p < kOffB2) {
+        const int i = (p - kOffW2) / kMlpHidden, o = (p - kOffW2) % kMlpHidden;
+        put(8 + 4 * (o >> 4) + (i >> 5), 16 * grp(i) + (o & 15), elt(i));
+        put(56 + 4 * (i >> 4) + (o >> 5), 16 * grp(o) + (i & 15), elt(o));
+    } else if (p >= kOffW3 && p < kOffB3) {
+        const int i = (p - kOffW3) / kMlpOut, o = (p - kOffW3) % kMlpOut;
+        put(40 + 4 * (o >> 4) + (i >> 5), 16 * grp(i) + (o & 15), elt(i));
+        put(48 + (i >> 4), 16 * grp(o) + (i & 15), elt(o));
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) k_pack_train(const float *__restrict__ P, __bf16 *__restrict__ img)
+{
+    const int p = blockIdx.x * kBlock + threadIdx.x;
+    if (p < kMlpParams) pack_train(img, p, P[p]);
+}
+
+// One operand slot (high and low part) of a lane, and the split product with it.
+struct Slot {
+    bf16x8 hi, lo;
+};
+__device__ __forceinline__ Slot slot_at(const uint4 *img, int slot, int lane)
+{
+    return {__builtin_bit_cast(bf16x8, img[(slot * 2) * 64 + lane]),
+            __builtin_bit_cast(bf16x8, img[(slot * 2 + 1) * 64 + lane])};
+}
+__device__ __forceinline__ f32x4v mfma3_16(const Slot &a, const Slot &b, f32x4v c)
+{
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, b.hi, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, b.lo, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.lo, b.hi, c, 0, 0, 0);
+    return c;
+}
+
+// What a training pass leaves for the weight gradients: per layer the inputs
+// (u, h1, h2) and the gradients of the pre-activations (d1, d2, dy), 16 samples
+// after 16, the 16 values of a unit together, so that the operand of 32 units
+// by 16 samples is one run of 2 KB (with a unit's whole batch in one run a load
+// touches 32 lines).  Mp samples, a multiple of 32, zeros past the batch.
+struct TrainBufs {
+    float *u, *h1, *h2, *d1, *d2, *dy;   // kTrainIn, 4 x 128 and kTrainOut units
+    float *part;                         // [chunks][kPartStride] weight-gradient sums
+    float *loss;                         // [Mp / 16], one per 16 samples
+    int64_t Mp;
+    int chunks, chunk;                   // chunk: samples per chunk, a multiple of 32
+};
+constexpr int kTrainIn = 8, kTrainOut = 32;   // units stored for the features and the outputs
+constexpr int kPartStride = (kMlpParams + 63) / 64 * 64;
+
+// Forward pass of 16 samples per workgroup, and with TRAIN the loss
+//   L = mean_{b,k} (y - t)^2 + mu mean_b [(sum_k y - 1)^2 + sum_d (sum_k y s_dk)^2]
+// (one partial sum per workgroup) and the backward pass.  What bounds it is
+// latency: a batch of 8192 is 512 groups of samples, and each is a chain of
+// five matrix products.  So the 128 units of a layer are shared out over four
+// wavefronts, 32 each (lane l: sample l % 16, eight units), which is one k
+// block of the next product: its split operand goes to the others through
+// LDS, one barrier a layer.  The weights a wavefront needs next are requested
+// a layer ahead.  8192 samples: 16 us; with all units in one wavefront 33 us,
+// and as one product kernel per layer with activations through memory 290 us.
+constexpr int kPassWaves = 4;
+template <bool TRAIN>
+__global__ void __launch_bounds__(64 * kPassWaves)
+k_mlp_pass(int64_t M, const float *__restrict__ feat, int64_t rows, const int64_t *__restrict__ idx,
+           const float *__restrict__ norm, const float *__restrict__ P, const uint4 *__restrict__ img,
+           const float *__restrict__ target, float mu, float *__restrict__ Y, const TrainBufs tb, ErrWord *err)
+{
+    __shared__ bf16x8 ops[TRAIN ? 3 : 2][4][2][64];   // h1, h2 and d2 as operands
+    const int lane = threadIdx.x & 63, s = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t b = (int64_t)blockIdx.x * 16 + s;
+    const bool in = b < M;
+    // place of this lane's sample and unit i in a buffer of `units` units
+    auto at = [&](int units, int i) { return ((int64_t)blockIdx.x * units + i) * 16 + s; };
+    Slot w1[2], w2[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) w1[t] = slot_at(img, 2 * w + t, lane);
+    int64_t row = 0;
+    if (in) row = w == 0 && g == 0 ? batch_row(idx, b, rows, err) : (idx ? idx[b] : b);
+    if (row < 0 || row >= rows) row = 0;   // reported by batch_row
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) w2[t][kb] = slot_at(img, 8 + 4 * (2 * w + t) + kb, lane);
+    float f[6];
+    Slot u;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) f[q] = feat[row * 6 + q];
+    float tg[8];   // this lane's targets (outputs 16 (q / 4) + 4 g + q % 4)
+    if constexpr (TRAIN) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = 16 * (q >> 2) + 4 * g + (q & 3);
+            tg[q] = target[row * kMlpOut + (k < kMlpOut ? k : 0)];
         }
-        const float r0 = sy - 1.0f;
-        const float inv_m = 1.0f / (float)M;
-        acc = se * inv_m * (1.0f / kNe) + mu * inv_m * (r0 * r0 + r1[0] * r1[0] + r1[1] * r1[1] + r1[2] * r1[2]);
-        const float ce = 2.0f * inv_m * (1.0f / kNe), cr = 2.0f * mu * inv_m;
-        for (int k = 0; k < kNe; ++k)
-            dY[b * kNe + k] = ce * (y[k] - t[k]) +
-                              cr * (r0 + r1[0] * s[0][k % 3] + r1[1] * s[1][(k / 3) % 3] + r1[2] * s[2][k / 9]);
     }
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float v = 0.0f;
+        if (i < kMlpIn) v = in ? (f[i] - norm[i]) * norm[6 + i] : 0.0f;
+        if (TRAIN && i < kMlpIn && w == 0 && g == 0) tb.u[at(kTrainIn, i)] = v;
+        __bf16 p, r;
+        split_bf16(g == 0 ? v : 0.0f, p, r);
+        u.hi[i] = p; u.lo[i] = r;
+    }
+    float g1[TRAIN ? 8 : 1], g2[TRAIN ? 8 : 1];
+    // activations of this wavefront's 32 units: k block w of the next operand,
+    // and in training the derivatives and stored values
+    auto activate = [&](const f32x4v (&z)[2], float *gr, float *h, int to) {
+        Slot o;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            float a;
+            if constexpr (TRAIN) {
+                a = gelu(z[q >> 2][q & 3], gr[q]);
+                h[at(kMlpHidden, 32 * w + 16 * (q >> 2) + 4 * g + (q & 3))] = a;
+            } else {
+                a = gelu(z[q >> 2][q & 3]);
+            }
+            __bf16 p, r;
+            split_bf16(a, p, r);
+            o.hi[q] = p; o.lo[q] = r;
+        }
+        ops[to][w][0][lane] = o.hi;
+        ops[to][w][1][lane] = o.lo;
+    };
+    f32x4v z[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        z[t] = mfma3_16(w1[t], u, *reinterpret_cast<const f32x4v *>(P + kOffB1 + 32 * w + 16 * t + 4 * g));
+    activate(z, g1, tb.h1, 0);
+    Slot w3[TRAIN ? 2 : 1][4];   // forward only: wavefronts 0 and 1 take an output tile each
+#pragma unroll
+    for (int t = 0; t < (TRAIN ? 2 : 1); ++t)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) w3[t][kb] = slot_at(img, 40 + 4 * (TRAIN ? t : (w & 1)) + kb, lane);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) z[t] = *reinterpret_cast<const f32x4v *>(P + kOffB2 + 32 * w + 16 * t + 4 * g);
     __syncthreads();
-    if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-__global__ void k_sum_partials(int nb, const float *__restrict__ partial, float *__restrict__ out)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        float s = 0.0f;
-        for (int i = 0; i < nb; ++i) s += partial[i];
-        *out = s;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        const Slot o = {ops[0][kb][0][lane], ops[0][kb][1][lane]};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) z[t] = mfma3_16(w2[t][kb], o, z[t]);
+    }
+    activate(z, g2, tb.h2, 1);
+    if constexpr (!TRAIN) {
+        __syncthreads();
+        if (w >= 2) return;
+        f32x4v y;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = 16 * w + 4 * g + j < kMlpOut ? P[kOffB3 + 16 * w + 4 * g + j] : 0.0f;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) y = mfma3_16(w3[0][kb], Slot{ops[1][kb][0][lane], ops[1][kb][1][lane]}, y);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 16 * w + 4 * g + j;
+            if (in && k < kMlpOut) Y[b * kMlpOut + k] = y[j];
+        }
+        return;
+    } else {
+        Slot v3[2], v2[2][4];   // W3 and W2 for the way back
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            v3[t] = slot_at(img, 48 + 2 * w + t, lane);
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) v2[t][kb] = slot_at(img, 56 + 4 * (2 * w + t) + kb, lane);
+        }
+        f32x4v y[2];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = 16 * (q >> 2) + 4 * g + (q & 3);
+            y[q >> 2][q & 3] = k < kMlpOut ? P[kOffB3 + k] : 0.0f;
+        }
+        __syncthreads();
+        // every wavefront forms all outputs (24 products more, no exchange)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            const Slot o = {ops[1][kb][0][lane], ops[1][kb][1][lane]};
+#pragma unroll
+            for (int t = 0; t < 2; ++t) y[t] = mfma3_16(w3[t][kb], o, y[t]);
+        }
+        // loss and dL/dy; a sample's outputs are spread over lanes s, s + 16, ...
+        float sn[3][3];
+        node_offsets(f, sn);
+        float e[8], sx[8], sy[8], sz[8];
+        float se = 0.0f, r0 = 0.0f, r1 = 0.0f, r2 = 0.0f, r3 = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = 16 * (q >> 2) + 4 * g + (q & 3);
+            const bool out = k < kMlpOut;
+            const float yv = out ? y[q >> 2][q & 3] : 0.0f;
+            e[q] = out ? yv - tg[q] : 0.0f;
+            const int ax = k % 3, ay = (k / 3) % 3, az = k / 9;
+            sx[q] = ax == 0 ? sn[0][0] : (ax == 1 ? sn[0][1] : sn[0][2]);
+            sy[q] = ay == 0 ? sn[1][0] : (ay == 1 ? sn[1][1] : sn[1][2]);
+            sz[q] = az == 0 ? sn[2][0] : (az == 1 ? sn[2][1] : sn[2][2]);
+            se += e[q] * e[q];
+            r0 += yv; r1 += yv * sx[q]; r2 += yv * sy[q]; r3 += yv * sz[q];
+        }
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+            se += __shfl_xor(se, o);
+            r0 += __shfl_xor(r0, o); r1 += __shfl_xor(r1, o); r2 += __shfl_xor(r2, o); r3 += __shfl_xor(r3, o);
+        }
+        r0 -= 1.0f;
+        const float inv_m = 1.0f / (float)M;
+        float l = in && g == 0 ? se * inv_m * (1.0f / kNe) + mu * inv_m * (r0 * r0 + r1 * r1 + r2 * r2 + r3 * r3) : 0.0f;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) l += __shfl_xor(l, o);
+        if (w == 0 && lane == 0) tb.loss[blockIdx.x] = l;
+        const float ce = 2.0f * inv_m * (1.0f / kNe), cr = 2.0f * mu * inv_m;
+        Slot dy;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = 16 * (q >> 2) + 4 * g + (q & 3);
+            const float d = in && k < kMlpOut ? ce * e[q] + cr * (r0 + r1 * sx[q] + r2 * sy[q] + r3 * sz[q]) : 0.0f;
+            if (w == 0) tb.dy[at(kTrainOut, k)] = d;
+            __bf16 p, r;
+            split_bf16(d, p, r);
+            dy.hi[q] = p; dy.lo[q] = r;
+        }
+        // back through the layers: d2 = (W3 dy) gelu'(z2), d1 = (W2 d2) gelu'(z1)
+        Slot o;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) z[t] = mfma3_16(v3[t], dy, f32x4v{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float v = z[q >> 2][q & 3] * g2[q];
+            tb.d2[at(kMlpHidden, 32 * w + 16 * (q >> 2) + 4 * g + (q & 3))] = v;
+            __bf16 p, r;
+            split_bf16(v, p, r);
+            o.hi[q] = p; o.lo[q] = r;
+        }
+        ops[2][w][0][lane] = o.hi;
+        ops[2][w][1][lane] = o.lo;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) z[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            const Slot d = {ops[2][kb][0][lane], ops[2][kb][1][lane]};
+#pragma unroll
+            for (int t = 0; t < 2; ++t) z[t] = mfma3_16(v2[t][kb], d, z[t]);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            tb.d1[at(kMlpHidden, 32 * w + 16 * (q >> 2) + 4 * g + (q & 3))] = z[q >> 2][q & 3] * g1[q];
     }
 }
 
-// Adam (Kingma & Ba, 2015) on the flat FP32 parameter vector; c1, c2 are the
-// bias corrections 1 - beta^t.
-__global__ void k_adam(int64_t n, float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m1,
-                       float *__restrict__ m2, float lr, float b1, float b2, float eps, float c1, float c2)
+// Weight gradients of one chunk of samples: [dW; db](i, o) = sum_s X(i, s)
+// D(o, s) for RT x CT tiles of 32 x 32, with the bias gradient (the sum of D)
+// by the wavefront that holds the first rows.  Operands are split as they are
+// loaded; v_mfma_f32_32x32x16_bf16: lane l holds row / column l % 32 and
+// samples 8 (l / 32) + i; result register j is row 8 (j / 4) + 4 (l / 32) +
+// j % 4, column l % 32.
+template <int RT, int CT>
+__device__ __forceinline__ void wgrad_tiles(const float *__restrict__ X, int x_units, int x_rows,
+                                            const float *__restrict__ D, int d_units, int64_t beg, int64_t end,
+                                            float *__restrict__ W, int n_out, int stride, float *__restrict__ bias)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float a = b1 * m1[i] + (1.0f - b1) * gi;
-        const float b = b2 * m2[i] + (1.0f - b2) * gi * gi;
-        m1[i] = a;
-        m2[i] = b;
-        p[i] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    f32x16 acc[RT][CT] = {};
+    float bsum[CT] = {};
+    auto load8 = [&](const float *p, bool on, float (&v)[8]) {
+        const float4 a = on ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 c = on ? *reinterpret_cast<const float4 *>(p + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
+    };
+    auto split8 = [](const float (&v)[8], bf16x8 &hi, bf16x8 &lo) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __bf16 p, q;
+            split_bf16(v[i], p, q);
+            hi[i] = p; lo[i] = q;
+        }
+    };
+    // the loads of kAhead products are in flight together
+    constexpr int kAhead = 4;
+    for (int64_t s0 = beg; s0 < end; s0 += 16 * kAhead) {
+        float xv[kAhead][RT][8], dv[kAhead][CT][8];
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) {
+            const int64_t blk = (s0 >> 4) + n;
+            const bool on = s0 + 16 * n < end;
+#pragma unroll
+            for (int q = 0; q < RT; ++q) load8(X + ((blk * x_units + 32 * q + r) << 4) + 8 * h, on && 32 * q + r < x_rows, xv[n][q]);
+#pragma unroll
+            for (int q = 0; q < CT; ++q) load8(D + ((blk * d_units + 32 * q + r) << 4) + 8 * h, on, dv[n][q]);
+        }
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) {
+            bf16x8 dh[CT], dl[CT];
+#pragma unroll
+            for (int q = 0; q < CT; ++q) {
+                const float(&d)[8] = dv[n][q];
+                split8(d, dh[q], dl[q]);
+                bsum[q] += ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]));
+            }
+#pragma unroll
+            for (int q = 0; q < RT; ++q) {
+                bf16x8 xh, xl;
+                split8(xv[n][q], xh, xl);
+#pragma unroll
+                for (int t = 0; t < CT; ++t) acc[q][t] = mfma3(xh, xl, dh[t], dl[t], acc[q][t]);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int i = 32 * q + 8 * (j / 4) + 4 * h + (j % 4), o = 32 * t + r;
+                if (i < x_rows && o < n_out) W[(int64_t)i * stride + o] = acc[q][t][j];
+            }
+    if (bias) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            const float v = bsum[t] + __shfl_xor(bsum[t], 32);
+            if (h == 0 && 32 * t + r < n_out) bias[32 * t + r] = v;
+        }
+    }
+}
+
+// One wavefront per (job, chunk), two tiles each so that four rounds of loads
+// fit the registers at once: jobs 0..7 the row tiles and column halves of dW2,
+// 8 and 9 the row halves of dW3, 10 and 11 the column halves of dW1.  At most
+// 64 chunks of at least 128 samples: 768 wavefronts for a batch of 8192
+// (8 us).
+constexpr int kWgradJobs = 12;
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) k_mlp_wgrad(const TrainBufs tb)
+{
+    // the jobs of a chunk run on one XCD (workgroup b runs on XCD b % 8), whose
+    // L2 then reads the chunk from memory once instead of all eight (9.4 -> 7.9
+    // us for a batch of 8192)
+    const int job = (blockIdx.x >> 3) % kWgradJobs, ch = (blockIdx.x >> 3) / kWgradJobs * 8 + (blockIdx.x & 7);
+    if (ch >= tb.chunks) return;
+    const int64_t beg = (int64_t)ch * tb.chunk, end = min(beg + tb.chunk, tb.Mp);
+    float *P = tb.part + (int64_t)ch * kPartStride;
+    if (job < 8) {
+        const int i0 = (job & 3) * 32, o0 = (job >> 2) * 64;
+        wgrad_tiles<1, 2>(tb.h1 + i0 * 16, kMlpHidden, 32, tb.d2 + o0 * 16, kMlpHidden, beg, end,
+                          P + kOffW2 + i0 * kMlpHidden + o0, 64, kMlpHidden, i0 == 0 ? P + kOffB2 + o0 : nullptr);
+    } else if (job < 10) {
+        const int i0 = (job - 8) * 64;
+        wgrad_tiles<2, 1>(tb.h2 + i0 * 16, kMlpHidden, 64, tb.dy, kTrainOut, beg, end, P + kOffW3 + i0 * kMlpOut,
+                          kMlpOut, kMlpOut, i0 == 0 ? P + kOffB3 : nullptr);
+    } else {
+        const int o0 = (job - 10) * 64;
+        wgrad_tiles<1, 2>(tb.u, kTrainIn, kMlpIn, tb.d1 + o0 * 16, kMlpHidden, beg, end, P + kOffW1 + o0, 64,
+                          kMlpHidden, P + kOffB1 + o0);
+    }
+}
+
+// Adam (Kingma & Ba, 2015): learning rate, betas, bias corrections 1 - beta^t.
+struct AdamArgs {
+    float *p, *m1, *m2;
+    __bf16 *img;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// Sums the chunks of every parameter's gradient: four threads a quarter of the
+// chunks each, in order, then the quarters in order (one thread per parameter
+// waits for 64 loads in a row, 8 us instead of 5).  ADAM: updates the parameter
+// and its places in the packed operands; else stores the gradient.  The last
+// workgroup sums the loss (each thread a strided share in order, then a fixed
+// tree).
+constexpr int kUpdateBlock = 256;
+template <bool ADAM>
+__global__ void __launch_bounds__(kUpdateBlock)
+k_mlp_update(const TrainBufs tb, float *__restrict__ grad, const AdamArgs ad, float *__restrict__ loss)
+{
+    __shared__ float sh[kUpdateBlock];
+    if (blockIdx.x == gridDim.x - 1) {
+        float a = 0.0f;
+        for (int64_t i = threadIdx.x; i < tb.Mp / 16; i += kUpdateBlock) a += tb.loss[i];
+        sh[threadIdx.x] = a;
+        for (int o = kUpdateBlock / 2; o > 0; o >>= 1) {
+            __syncthreads();
+            if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        }
+        if (threadIdx.x == 0) *loss = sh[0];
+        return;
+    }
+    const int p = blockIdx.x * 64 + (threadIdx.x & 63), quarter = threadIdx.x >> 6;
+    const int per = (tb.chunks + 3) / 4;
+    const int c0 = quarter * per, c1 = min(c0 + per, tb.chunks);
+    float sum = 0.0f;   // (rows of kPartStride floats, a multiple of 64: p is in bounds)
+#pragma unroll 16
+    for (int c = c0; c < c1; ++c) sum += tb.part[(int64_t)c * kPartStride + p];
+    sh[threadIdx.x] = sum;
+    __syncthreads();
+    if (quarter > 0 || p >= kMlpParams) return;
+    const float gi = ((sh[p & 63] + sh[64 + (p & 63)]) + sh[128 + (p & 63)]) + sh[192 + (p & 63)];
+    if constexpr (!ADAM) {
+        grad[p] = gi;
+    } else {
+        const float a = ad.b1 * ad.m1[p] + (1.0f - ad.b1) * gi;
+        const float q = ad.b2 * ad.m2[p] + (1.0f - ad.b2) * gi * gi;
+        ad.m1[p] = a;
+        ad.m2[p] = q;
+        const float v = ad.p[p] - ad.lr * (a / ad.c1) / (sqrtf(q / ad.c2) + ad.eps);
+        ad.p[p] = v;
+        pack_train(ad.img, p, v);
     }
 }
 
@@ -671,19 +962,26 @@ hipError_t mlp_alloc(Ctx &c)
 {
     Mlp &net = c.mlp;
     if (net.params) return hipSuccess;
-    const size_t floats = 4 * (size_t)kMlpParams + 12 + 4;
+    const size_t floats = 3 * (size_t)kMlpParams + 12 + 4;
     const size_t head = (floats * sizeof(float) + 255) & ~(size_t)255;
     char *block = nullptr;
-    hipError_t e = hipMalloc((void **)&block, head + kMlpImageBytes);
+    const size_t image = (kMlpImageBytes + 255) & ~(size_t)255;
+    hipError_t e = hipMalloc((void **)&block, head + image + kTrainImageBytes);
     if (e != hipSuccess) return e;
     float *fp = reinterpret_cast<float *>(block);
     net.params = fp;
-    net.grad = fp + kMlpParams;
-    net.m1 = fp + 2 * kMlpParams;
-    net.m2 = fp + 3 * kMlpParams;
-    net.norm = fp + 4 * kMlpParams;
+    net.m1 = fp + kMlpParams;
+    net.m2 = fp + 2 * kMlpParams;
+    net.norm = fp + 3 * kMlpParams;
     net.loss = net.norm + 12;
     net.image = block + head;
+    net.train_image = block + head + image;
+    e = hipMemset(net.train_image, 0, kTrainImageBytes);   // slots of no parameter stay zero
+    if (e != hipSuccess) {
+        hipFree(block);
+        net.params = nullptr;
+        return e;
+    }
     float tab[4 * kGeluIntervals];
     gelu_table(tab);
     e = hipMemcpy(static_cast<char *>(net.image) + kMlpImageTableOffset, tab, sizeof(tab), hipMemcpyHostToDevice);
@@ -759,37 +1057,36 @@ hipError_t launch_features(const Ctx &c, int64_t n, const float *x, const float 
     return hipGetLastError();
 }
 
-// Scratch layout for batches of up to cap samples: split-product chunks,
-// then U (6 M), Z1, H1, Z2, H2 (128 M each), Y (27 M), dY (27 M) and the
-// loss partials.
-static int64_t part_floats(int64_t cap)
+// Samples of a batch as the training buffers hold them, and its chunks.
+static int64_t train_pad(int64_t M) { return (M + 31) / 32 * 32; }
+static int train_chunk(int64_t Mp)
 {
-    const int64_t chunks = (cap + kSplitChunk - 1) / kSplitChunk;
-    return chunks * (kMlpHidden + 1) * kMlpHidden;
+    const int64_t c = std::max<int64_t>(128, (Mp + 63) / 64);
+    return (int)((c + 31) / 32 * 32);
 }
 
-// Matrix product C = A B (+ ones row, see k_gemm).  A k range longer than
-// one chunk is split when C has few tiles; the chunks go to the head of the
-// training scratch and are summed in order into C, which is then row-major
-// (scm = N, scn = 1).
-static void gemm(Ctx &c, hipStream_t s, int Ma, int ones_row, int N, int K, const float *A, int64_t sam,
-                 int64_t sak, const float *B, int64_t sbk, int64_t sbn, float *C, int64_t scm, int64_t scn)
+static size_t train_floats(int64_t M)
 {
-    const int M = Ma + ones_row;
-    const int tiles = ((M + 31) / 32) * ((N + 31) / 32);
-    const int bx = (tiles + 3) / 4;
-    const int chunks = (K + kSplitChunk - 1) / kSplitChunk;
-    if (chunks <= 1 || tiles >= 256) {
-        hipLaunchKernelGGL(k_gemm, dim3(bx, 1), dim3(kBlock), 0, s, Ma, ones_row, N, K, K > 0 ? K : 1, A, sam, sak, B,
-                           sbk, sbn, C, scm, scn, (int64_t)0);
-        return;
-    }
-    float *part = c.mlp.scratch;
-    hipLaunchKernelGGL(k_gemm, dim3(bx, chunks), dim3(kBlock), 0, s, Ma, ones_row, N, K, kSplitChunk, A, sam, sak, B,
-                       sbk, sbn, part, (int64_t)N, (int64_t)1, (int64_t)M * N);
-    const int64_t count = (int64_t)M * N;
-    hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, count,
-                       chunks, part, C);
+    const int64_t Mp = train_pad(M);
+    const int64_t chunks = (Mp + train_chunk(Mp) - 1) / train_chunk(Mp);
+    return (size_t)(Mp * (kTrainIn + 4 * kMlpHidden + kTrainOut) + chunks * kPartStride + Mp / 16 + 64);
+}
+
+static TrainBufs train_bufs(const Ctx &c, int64_t M)
+{
+    TrainBufs t;
+    t.Mp = train_pad(M);
+    t.chunk = train_chunk(t.Mp);
+    t.chunks = (int)((t.Mp + t.chunk - 1) / t.chunk);
+    t.u = c.mlp.scratch;
+    t.h1 = t.u + kTrainIn * t.Mp;
+    t.h2 = t.h1 + kMlpHidden * t.Mp;
+    t.d1 = t.h2 + kMlpHidden * t.Mp;
+    t.d2 = t.d1 + kMlpHidden * t.Mp;
+    t.dy = t.d2 + kMlpHidden * t.Mp;
+    t.part = t.dy + kTrainOut * t.Mp;
+    t.loss = t.part + (int64_t)t.chunks * kPartStride;
+    return t;
 }
 
 hipError_t mlp_reserve(Ctx &c, int64_t M)
@@ -802,30 +1099,23 @@ hipError_t mlp_reserve(Ctx &c, int64_t M)
     if (net.scratch) hipFree(net.scratch);
     net.scratch = nullptr;
     net.cap_batch = 0;
-    const int64_t per = 6 + 4 * kMlpHidden + 2 * kMlpOut;
-    const int64_t floats = part_floats(M) + per * M + (M + kBlock - 1) / kBlock + 64;
-    e = hipMalloc((void **)&net.scratch, (size_t)floats * sizeof(float));
+    // enough for any smaller batch too: its samples take less, its chunks at most 64
+    const size_t floats = train_floats(M) + (size_t)64 * kPartStride;
+    e = hipMalloc((void **)&net.scratch, floats * sizeof(float));
     if (e != hipSuccess) return e;
     net.cap_batch = M;
     return hipSuccess;
 }
 
-struct Acts {
-    float *U, *Z1, *H1, *Z2, *H2, *Y, *dY, *partial;
-};
-
-static Acts acts(Ctx &c, int64_t M)
+// The packed training operands follow the parameters: Adam refreshes them as
+// it goes, a load leaves them to the next training call.
+static void pack_train_if_stale(Ctx &c, hipStream_t s)
 {
-    Acts a;
-    a.U = c.mlp.scratch + part_floats(c.mlp.cap_batch);
-    a.Z1 = a.U + 6 * M;
-    a.H1 = a.Z1 + kMlpHidden * M;
-    a.Z2 = a.H1 + kMlpHidden * M;
-    a.H2 = a.Z2 + kMlpHidden * M;
-    a.Y = a.H2 + kMlpHidden * M;
-    a.dY = a.Y + kMlpOut * M;
-    a.partial = a.dY + kMlpOut * M;
-    return a;
+    Mlp &net = c.mlp;
+    if (net.train_version == net.version) return;
+    hipLaunchKernelGGL(k_pack_train, dim3((kMlpParams + kBlock - 1) / kBlock), dim3(kBlock), 0, s, net.params,
+                       static_cast<__bf16 *>(net.train_image));
+    net.train_version = net.version;
 }
 
 hipError_t mlp_forward_batch(Ctx &c, int64_t M, const float *feat, int64_t rows, const int64_t *idx, float *Yout,
@@ -833,61 +1123,54 @@ hipError_t mlp_forward_batch(Ctx &c, int64_t M, const float *feat, int64_t rows,
 {
     if (M == 0) return hipSuccess;
     Mlp &net = c.mlp;
-    const int H = kMlpHidden;
-    const Acts a = acts(c, M);
-    float *Y = Yout ? Yout : a.Y;
-    const float *P = net.params;
-    const int g = grid_for(M * H, c.cu_count);
-    hipLaunchKernelGGL(k_normalize, dim3(grid_for(M * 6, c.cu_count)), dim3(kBlock), 0, s, M, feat, rows, idx,
-                       net.norm, a.U, c.err);
-    gemm(c, s, (int)M, 0, H, kMlpIn, a.U, kMlpIn, 1, P + kOffW1, H, 1, a.Z1, H, 1);
-    hipLaunchKernelGGL(k_bias_act, dim3(g), dim3(kBlock), 0, s, M, H, a.Z1, a.H1, P + kOffB1);
-    gemm(c, s, (int)M, 0, H, H, a.H1, H, 1, P + kOffW2, H, 1, a.Z2, H, 1);
-    hipLaunchKernelGGL(k_bias_act, dim3(g), dim3(kBlock), 0, s, M, H, a.Z2, a.H2, P + kOffB2);
-    gemm(c, s, (int)M, 0, kMlpOut, H, a.H2, H, 1, P + kOffW3, kMlpOut, 1, Y, kMlpOut, 1);
-    hipLaunchKernelGGL(k_bias_act, dim3(grid_for(M * kMlpOut, c.cu_count)), dim3(kBlock), 0, s, M, kMlpOut, Y,
-                       (float *)nullptr, P + kOffB3);
+    pack_train_if_stale(c, s);
+    hipLaunchKernelGGL(k_mlp_pass<false>, dim3((unsigned)((M + 15) / 16)), dim3(64 * kPassWaves), 0, s, M, feat,
+                       rows, idx, net.norm, net.params, static_cast<const uint4 *>(net.train_image), nullptr, 0.0f, Yout,
+                       TrainBufs{}, c.err);
     return hipGetLastError();
 }
+
+// Forward, backward and the chunks of the weight gradients of a batch.
+static TrainBufs launch_train_pass(Ctx &c, int64_t M, const float *feat, const float *target, int64_t rows,
+                                   const int64_t *idx, float mu, hipStream_t s)
+{
+    Mlp &net = c.mlp;
+    pack_train_if_stale(c, s);
+    const TrainBufs tb = train_bufs(c, M);
+    hipLaunchKernelGGL(k_mlp_pass<true>, dim3((unsigned)(tb.Mp / 16)), dim3(64 * kPassWaves), 0, s, M, feat, rows,
+                       idx, net.norm, net.params, static_cast<const uint4 *>(net.train_image), target, mu, nullptr, tb, c.err);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kWgradJobs * round_up8(tb.chunks))), dim3(64), 0, s, tb);
+    return tb;
+}
+
+constexpr unsigned kUpdateBlocks = (kMlpParams + 63) / 64 + 1;   // and one for the loss
 
 hipError_t mlp_grad_batch(Ctx &c, int64_t M, const float *feat, const float *target, int64_t rows,
                           const int64_t *idx, float mu, float *grad, float *loss, hipStream_t s)
 {
     if (M == 0) return hipSuccess;
-    Mlp &net = c.mlp;
-    const int H = kMlpHidden;
-    hipError_t e = mlp_forward_batch(c, M, feat, rows, idx, nullptr, s);
-    if (e != hipSuccess) return e;
-    const Acts a = acts(c, M);
-    const float *P = net.params;
-    const int nb = (int)((M + kBlock - 1) / kBlock);
-    const int g = grid_for(M * H, c.cu_count);
-    hipLaunchKernelGGL(k_loss_grad, dim3(nb), dim3(kBlock), 0, s, M, a.Y, target, feat, rows, idx, mu, a.dY,
-                       a.partial, c.err);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, s, nb, a.partial, loss);
-    // layer 3: [dW3; db3] = [H2 1]^T dY; dZ2 = (dY W3^T) gelu'(Z2), written over H2
-    gemm(c, s, H, 1, kMlpOut, (int)M, a.H2, 1, H, a.dY, kMlpOut, 1, grad + kOffW3, kMlpOut, 1);
-    gemm(c, s, (int)M, 0, H, kMlpOut, a.dY, kMlpOut, 1, P + kOffW3, 1, kMlpOut, a.H2, H, 1);
-    hipLaunchKernelGGL(k_gelu_bwd, dim3(g), dim3(kBlock), 0, s, M * H, a.H2, a.Z2);
-    // layer 2: [dW2; db2] = [H1 1]^T dZ2; dZ1 = (dZ2 W2^T) gelu'(Z1), written over H1
-    gemm(c, s, H, 1, H, (int)M, a.H1, 1, H, a.H2, H, 1, grad + kOffW2, H, 1);
-    gemm(c, s, (int)M, 0, H, H, a.H2, H, 1, P + kOffW2, 1, H, a.H1, H, 1);
-    hipLaunchKernelGGL(k_gelu_bwd, dim3(g), dim3(kBlock), 0, s, M * H, a.H1, a.Z1);
-    // layer 1: [dW1; db1] = [U 1]^T dZ1
-    gemm(c, s, kMlpIn, 1, H, (int)M, a.U, 1, kMlpIn, a.H1, H, 1, grad + kOffW1, H, 1);
+    const TrainBufs tb = launch_train_pass(c, M, feat, target, rows, idx, mu, s);
+    hipLaunchKernelGGL(k_mlp_update<false>, dim3(kUpdateBlocks), dim3(kUpdateBlock), 0, s, tb, grad, AdamArgs{}, loss);
     return hipGetLastError();
 }
 
-hipError_t mlp_adam(Ctx &c, float lr, hipStream_t s)
+hipError_t mlp_train_batch(Ctx &c, int64_t M, const float *feat, const float *target, int64_t rows,
+                           const int64_t *idx, float mu, float lr, float *loss, hipStream_t s)
 {
+    if (M == 0) return hipSuccess;
     Mlp &net = c.mlp;
+    const TrainBufs tb = launch_train_pass(c, M, feat, target, rows, idx, mu, s);
     net.adam_step += 1;
     const double b1 = 0.9, b2 = 0.999;
-    const float c1 = (float)(1.0 - std::pow(b1, (double)net.adam_step));
-    const float c2 = (float)(1.0 - std::pow(b2, (double)net.adam_step));
-    hipLaunchKernelGGL(k_adam, dim3(grid_for(kMlpParams, c.cu_count)), dim3(kBlock), 0, s, (int64_t)kMlpParams,
-                       net.params, net.grad, net.m1, net.m2, lr, (float)b1, (float)b2, 1e-8f, c1, c2);
+    AdamArgs ad;
+    ad.p = net.params; ad.m1 = net.m1; ad.m2 = net.m2;
+    ad.img = static_cast<__bf16 *>(net.train_image);
+    ad.lr = lr; ad.b1 = (float)b1; ad.b2 = (float)b2; ad.eps = 1e-8f;
+    ad.c1 = (float)(1.0 - std::pow(b1, (double)net.adam_step));
+    ad.c2 = (float)(1.0 - std::pow(b2, (double)net.adam_step));
+    hipLaunchKernelGGL(k_mlp_update<true>, dim3(kUpdateBlocks), dim3(kUpdateBlock), 0, s, tb, nullptr, ad, loss);
     net.version += 1;
+    net.train_version = net.version;
     return hipGetLastError();
 }
 
