@@ -325,15 +325,51 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
         c.opts = *opts;
     }
 
+    // ---- cell lookup: FP32 bound of uniform axes, buckets of stretched ones ----
+    std::vector<uint32_t> bucket[3];
+    for (int d = 0; d < 3; ++d) {
+        Axis &a = c.g.ax[d];
+        const auto &f = c.h_faces[d];
+        const int n = a.n;
+        a.t_off = (float)a.f0;
+        a.t_scale = (float)a.inv_h;
+        a.t_eps = 1.0f;
+        if (a.uniform) {
+            // rounding of f0 and of the difference, of 1/h and of the product,
+            // and how far the faces lie from f0 + i h
+            const double ulp = 5.9604644775390625e-8;   // 2^-24
+            double dev = 0.0;
+            for (int i = 0; i <= n; ++i) dev = std::max(dev, std::fabs(f[i] - (a.f0 + i * (a.L / n))));
+            const double eps = 1.01 * ulp * (std::fabs(a.f0) * a.inv_h + 3.0 * n) + dev * a.inv_h + 1e-6;
+            if (eps < 0.25) a.t_eps = (float)eps;
+        }
+        a.nbucket = 4 * n;
+        a.bucket_scale = a.nbucket / a.L;
+        if (!a.uniform) {
+            auto of = [&](double X) {
+                return std::min(std::max((int)((X - a.f0) * a.bucket_scale), 0), a.nbucket - 1);
+            };
+            bucket[d].resize(a.nbucket);
+            for (int b = 0, k = 0; b < a.nbucket; ++b) {
+                // first cell that ends in bucket b or later, last that starts in b or before
+                while (k < n - 1 && of(f[k + 1]) < b) ++k;
+                int q = k;
+                while (q < n - 1 && of(f[q + 1]) <= b) ++q;
+                bucket[d][b] = (uint32_t)k | (uint32_t)q << 16;
+            }
+        }
+    }
+
     // ---- device geometry block ----
     size_t bytes = 0;
-    size_t off_f[3], off_c[3], off_wc[3], off_wf[3];
+    size_t off_f[3], off_c[3], off_wc[3], off_wf[3], off_b[3];
     auto take = [&](size_t nbytes) { size_t o = bytes; bytes += (nbytes + 255) & ~size_t(255); return o; };
     for (int d = 0; d < 3; ++d) {
         off_f[d] = take(c.h_faces[d].size() * sizeof(double));
         off_c[d] = take(c.h_centres[d].size() * sizeof(double));
         off_wc[d] = take(wc[d].size() * sizeof(float));
         off_wf[d] = take(wf[d].size() * sizeof(float));
+        off_b[d] = take(bucket[d].size() * sizeof(uint32_t));
     }
     std::vector<unsigned char> blob(bytes, 0);
     for (int d = 0; d < 3; ++d) {
@@ -341,6 +377,7 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
         memcpy(&blob[off_c[d]], c.h_centres[d].data(), c.h_centres[d].size() * sizeof(double));
         memcpy(&blob[off_wc[d]], wc[d].data(), wc[d].size() * sizeof(float));
         memcpy(&blob[off_wf[d]], wf[d].data(), wf[d].size() * sizeof(float));
+        if (!bucket[d].empty()) memcpy(&blob[off_b[d]], bucket[d].data(), bucket[d].size() * sizeof(uint32_t));
     }
     e = hipMalloc(&c.geom_block, bytes);
     if (e != hipSuccess) { delete ctx; return MLS_E_NOMEM; }
@@ -353,6 +390,7 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
         a.centres = reinterpret_cast<const double *>(base + off_c[d]);
         a.width_c = reinterpret_cast<const float *>(base + off_wc[d]);
         a.width_f = reinterpret_cast<const float *>(base + off_wf[d]);
+        a.bucket = bucket[d].empty() ? nullptr : reinterpret_cast<const uint32_t *>(base + off_b[d]);
     }
     if (hipMalloc((void **)&c.d_grid, sizeof(Grid)) != hipSuccess ||
         hipMemcpy(c.d_grid, &c.g, sizeof(Grid), hipMemcpyHostToDevice) != hipSuccess) {

@@ -53,6 +53,15 @@ struct Axis {
     const double *centres;  // n, 0.5 * (f[i] + f[i+1])
     const float *width_c;   // n     control-volume widths of centre nodes
     const float *width_f;   // n + 1 control-volume widths of face nodes
+    // Cell of an FP32 coordinate on a uniform axis in FP32: t = (x - t_off)
+    // t_scale errs by less than t_eps, so away from an integer by that much its
+    // floor is the cell (t_eps = 1: the axis does not qualify)
+    float t_off, t_scale, t_eps;
+    // Stretched axis: bucket floor((X - f0) bucket_scale) of nbucket equal ones
+    // holds cells bucket & 0xffff .. bucket >> 16
+    int32_t nbucket;
+    double bucket_scale;
+    const uint32_t *bucket;
 };
 
 struct Weight {

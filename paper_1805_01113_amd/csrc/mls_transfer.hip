@@ -192,15 +192,15 @@ k_bin_pos(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x, c
                     jy[l] = py;
                     jz[l] = pz;
                 }
-                const double p[3] = {(double)px, (double)py, (double)pz};
-                int cell[3];
+                const float p[3] = {px, py, pz};
+                int cell[3] = {0, 0, 0};
                 bool ok = true;
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    int ih = 0;
-                    double X;
-                    ok = ok && locate(g.ax[d], 0, p[d], ih, X);
-                    cell[d] = ih;
+                    // the cell is the centre-staggered home; both its
+                    // neighbours must exist on a wall axis
+                    ok = ok && cell_axis_f(g.ax[d], p[d], cell[d]);
+                    ok = ok && (g.ax[d].periodic || (cell[d] >= 1 && cell[d] + 1 < g.ax[d].n));
                 }
                 t = ok ? ((int64_t)tile_of(cell[2], itz) * g.ntile[1] + tile_of(cell[1], ity)) * g.ntile[0] +
                              tile_of(cell[0], itx)
