@@ -14,9 +14,11 @@
 // cell of several bodies ends at -1 (all but one body see a foreign id) and a
 // cell of one body keeps its id, bit for bit on any schedule.
 //
-// Bound by the pass over the markers (12 B each, their cells' lines) and the
-// cell lookup.  22.4 M markers in 1024^3: 0.10 ms a launch; entering with a
-// compare-and-swap per marker, which the memory side executes, took 0.75 ms.
+// Bound by memory: a pass reads 12-16 B per marker and about 19 B of its cells'
+// 128-byte lines (surfaces fill them sparsely), the first also writes those.
+// 22.4 M markers in 1024^3: 0.24 and 0.19 ms for the two launches, 5 TB/s;
+// entering with a compare-and-swap per marker, which the memory side executes,
+// took 0.75 ms.  Four markers a thread at a time change nothing.
 #include "mls_device.h"
 
 namespace mls {
