@@ -199,19 +199,64 @@ __device__ __forceinline__ bool interp_grad_fp64(const Grid &g, const Weight &Wt
     return ok;
 }
 
+// The same in FP32, for a support with a field value that is not finite: the
+// value summed over q_k, the gradient over q_k - q_home, node by node.
+__device__ __forceinline__ void interp_grad_direct(const Grid &g, const Weight &Wt, float tau, int c,
+                                                   const double p[3], const float *fq, const int64_t ox[3],
+                                                   const int64_t oy[3], const int64_t oz[3], float out[4])
+{
+    GradCoef<float> q;
+    int ih[3];
+    float kmax = 0.f;
+    grad_geo(g, c, p, q, ih);
+    grad_coef(Wt, tau, q, kmax);   // solved in FP32 by the first kernel
+    const float fh = fq[oz[1] + oy[1] + ox[1]];
+    for (int i = 0; i < 4; ++i) out[i] = 0.f;
+    for_each_node<false>(q, Wt, [&](int a, int b, int cz, float ph, const float dv[3]) {
+        const float fv = fq[oz[cz] + oy[b] + ox[a]], df = fv - fh;
+        out[0] += ph * fv;
+        out[1] += dv[0] * df; out[2] += dv[1] * df; out[3] += dv[2] * df;
+    });
+}
+
 __device__ __forceinline__ void count_fp64(DevStats *stats, unsigned long long routed)
 {
     if (routed) atomicAdd(&stat_slot(stats).fp64_solves, routed);
 }
 
-// FP64 queue: q[0] = entries, q[1 + i] = 4 l + c.
-__device__ __forceinline__ void enqueue(uint32_t *queue, int64_t l, int c)
+// Queue of the (marker, staggering) pairs that a second kernel redoes: q[0]
+// entries, q[1] the workgroups done with them, q[2 + i] = 4 l + c, with
+// kDirect set for a pair that only needs the sums node by node.  The second
+// kernel leaves both counts at zero for the next call.
+constexpr int kQueueHead = 2;
+constexpr uint32_t kDirect = 0x80000000u;   // 4 l + c stays below it (at most 0x1fffffff markers)
+
+// Appends e of every lane with on set, one reservation per wavefront; every
+// active lane calls it.
+__device__ __forceinline__ void enqueue(uint32_t *queue, bool on, uint32_t e)
 {
-    const uint32_t i = atomicAdd(&queue[0], 1u);
-    queue[1 + i] = (uint32_t)(4 * l + c);
+    const unsigned long long mask = __ballot(on);
+    if (!mask) return;
+    const int lane = threadIdx.x & 63, lead = __ffsll((long long)mask) - 1;
+    uint32_t slot = 0;
+    if (lane == lead) slot = atomicAdd(&queue[0], (uint32_t)__popcll(mask));
+    slot = __shfl(slot, lead);
+    if (on) queue[kQueueHead + slot + __popcll(mask & ((1ull << lane) - 1ull))] = e;
 }
 
-__global__ void k_queue_clear(uint32_t *queue) { if (threadIdx.x == 0) queue[0] = 0u; }
+__global__ void k_queue_clear(uint32_t *queue)
+{
+    if (threadIdx.x < kQueueHead) queue[threadIdx.x] = 0u;
+}
+
+// Called by every thread of the second kernel once it is done with the cnt
+// entries: the last workgroup clears the counts.
+__device__ __forceinline__ void queue_done(uint32_t *queue, uint32_t cnt)
+{
+    if (cnt == 0) return;
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(&queue[1], 1u) == gridDim.x - 1) queue[0] = queue[1] = 0u;
+}
 
 // Shape functions and derivatives of one staggering, blocked by 64 markers:
 // home[l], phi[(b*27 + k)*64 + r], dphi[((b*3 + d)*27 + k)*64 + r].
@@ -257,15 +302,103 @@ k_build_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int c, int64_t n
             });
         } else {
             ++routed;
-            enqueue(queue, l, c);
+            enqueue(queue, true, (uint32_t)(4 * l + c));
         }
     }
     count_fp64(stats, routed);
 }
 
+// Value (out[0]) and gradient (out[1 + d]) of a field over one support in
+// FP32, without forming the shape functions.  With df_k = q_k - q_home and the
+// vectors T = sum_k W_k p_k df_k and T_d = sum_k dW_dk p_k df_k, the solution
+// z of A z = T gives them all:
+//   value = q_home + sum_k phi_k df_k = q_home + z_0   (sum_k phi_k = 1),
+//   d/dxi_d = gamma . T_d + (beta_d - eta_d) . T = gamma . T_d + z_{1+d} - z . (dA_d gamma),
+// one solve instead of the seven of grad_coef.  (The sums over df instead of q
+// use sum_k dphi_dk = 0 and are O(h |grad q|) instead of O(|q|), which spares
+// FP32 the cancellation of an O(|q|/h) sum down to O(|grad q|).)  The weights
+// are products of three axes, so the 16 sums are contracted axis by axis: 237
+// multiply-adds for the 27 nodes, where visiting each node takes about 950
+// operations.  Returns false if the pair goes to FP64.
+__device__ __forceinline__ bool value_and_grad(const Weight &Wt, float tau, const float s[3][3], const float rH[3],
+                                               const float qv[kNe], float out[4], float &kmax)
+{
+    // per axis and node: w, w s, -w', -w' s (the factors of W_k p_k and dW_dk p_k)
+    float w0[3][3], w1[3][3], d0[3][3], d1[3][3];
+    Moments<float> m[3], md[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        float a0 = 0.f, a1 = 0.f, a2 = 0.f, b0 = 0.f, b1 = 0.f, b2 = 0.f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float v, dv;
+            weight1_ds(Wt, s[d][a], v, dv);
+            w0[d][a] = v;
+            w1[d][a] = v * s[d][a];
+            d0[d][a] = -dv;
+            d1[d][a] = -dv * s[d][a];
+            a0 += w0[d][a]; a1 += w1[d][a]; a2 += w1[d][a] * s[d][a];
+            b0 += d0[d][a]; b1 += d1[d][a]; b2 += d1[d][a] * s[d][a];
+        }
+        m[d] = {a0, a1, a2};
+        md[d] = {b0, b1, b2};
+    }
+    float A[10], L[10], gam[4];
+    assemble(m[0], m[1], m[2], A);
+    if (!cholesky4(A, L)) return false;
+    const float kap = cond_bound_and_gamma(A, L, gam);
+    kmax = fmaxf(kmax, isfinite(kap) ? kap : 3.0e38f);
+    if (!(kap <= tau)) return false;
+    // x, then y, then z: names give the factor kind per axis (0: w, 1: w s, 2: -w', 3: -w' s)
+    const float fh = qv[13];
+    float T[4] = {0.f, 0.f, 0.f, 0.f}, Tx[4] = {0.f, 0.f, 0.f, 0.f}, Ty[4] = {0.f, 0.f, 0.f, 0.f},
+          Tz[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        float p00 = 0.f, p10 = 0.f, p01 = 0.f, p20 = 0.f, p30 = 0.f, p21 = 0.f, p02 = 0.f, p12 = 0.f, p03 = 0.f;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            float r0 = 0.f, r1 = 0.f, r2 = 0.f, r3 = 0.f;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float df = qv[a + 3 * b + 9 * c] - fh;
+                r0 += w0[0][a] * df; r1 += w1[0][a] * df; r2 += d0[0][a] * df; r3 += d1[0][a] * df;
+            }
+            p00 += r0 * w0[1][b]; p10 += r1 * w0[1][b]; p01 += r0 * w1[1][b];
+            p20 += r2 * w0[1][b]; p30 += r3 * w0[1][b]; p21 += r2 * w1[1][b];
+            p02 += r0 * d0[1][b]; p12 += r1 * d0[1][b]; p03 += r0 * d1[1][b];
+        }
+        T[0] += p00 * w0[2][c]; T[1] += p10 * w0[2][c]; T[2] += p01 * w0[2][c]; T[3] += p00 * w1[2][c];
+        Tx[0] += p20 * w0[2][c]; Tx[1] += p30 * w0[2][c]; Tx[2] += p21 * w0[2][c]; Tx[3] += p20 * w1[2][c];
+        Ty[0] += p02 * w0[2][c]; Ty[1] += p12 * w0[2][c]; Ty[2] += p03 * w0[2][c]; Ty[3] += p02 * w1[2][c];
+        Tz[0] += p00 * d0[2][c]; Tz[1] += p10 * d0[2][c]; Tz[2] += p01 * d0[2][c]; Tz[3] += p00 * d1[2][c];
+    }
+    float z[4];
+    chol_solve(L, T, z);
+    out[0] = fh + z[0];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        float dA[10], v[4];
+        assemble(d == 0 ? md[0] : m[0], d == 1 ? md[1] : m[1], d == 2 ? md[2] : m[2], dA);
+        sym_mul(dA, gam, v);
+        const float *t = d == 0 ? Tx : (d == 1 ? Ty : Tz);
+        const float g = gam[0] * t[0] + gam[1] * t[1] + gam[2] * t[2] + gam[3] * t[3];
+        out[1 + d] = rH[d] * (g + (z[1 + d] - (z[0] * v[0] + z[1] * v[1] + z[2] * v[2] + z[3] * v[3])));
+    }
+    return true;
+}
+
 // Value and gradient of the MLS approximation of the fields at the markers:
-// for c in 0..nc-1 (u, v, w, then the cell-centred p when given),
+// for c in 0..NC-1 (u, v, w, then the cell-centred p when given),
 // val[c][l] = sum_k phi_k q_c[node_k], grad[3c + d][l] = sum_k dphi_dk q_c.
+// One wavefront per (64 markers, staggering), the staggerings of 64 markers
+// side by side on one XCD, so that few markers too reach all compute units.
+// Bound by the vector ALU.  2.56 M markers of a stretched channel with pressure
+// 0.36 ms, 20,480 markers without 9 us; with the node-by-node sums and all
+// staggerings in one wavefront 0.73 ms and 19 us.  A pair whose result is not
+// finite is queued for the node-by-node sums, which pass an infinite or NaN
+// field value on as they meet it.
+template <int NC>
 __global__ void __launch_bounds__(kGradBlock)
 k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, const float *__restrict__ x,
               const float *__restrict__ y, const float *__restrict__ z, const float *__restrict__ u,
@@ -274,54 +407,54 @@ k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, cons
               float *__restrict__ pgrad, uint32_t *queue, ErrWord *err, DevStats *stats)
 {
     const Grid &g = *gp;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int nc = pf ? 4 : 3;
+    const int gw = (int)xcd_block() * (kGradBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = gw % NC;
+    const int64_t stride = (int64_t)(gridDim.x * (kGradBlock / 64) / NC) * 64;
+    const float *fq = c == 0 ? u : (c == 1 ? v : (c == 2 ? w : pf));
+    float *vo = c < 3 ? (val ? val + (int64_t)c * n : nullptr) : pval;
+    float *go = c < 3 ? grad + (int64_t)3 * c * n : pgrad;
+    const int nx = comp_dim(g, c, 0), ny = comp_dim(g, c, 1), nz = comp_dim(g, c, 2);
     unsigned long long routed = 0;
     float kmax = 0.f;
-    for (int64_t l = xcd_block() * blockDim.x + threadIdx.x; l < n; l += stride) {
+    for (int64_t l = (int64_t)(gw / NC) * 64 + (threadIdx.x & 63); l < n; l += stride) {
         const double p[3] = {(double)x[l], (double)y[l], (double)z[l]};
-        for (int c = 0; c < nc; ++c) {
-            const float *fq = c == 0 ? u : (c == 1 ? v : (c == 2 ? w : pf));
-            float *vo = c < 3 ? val : pval;
-            float *go = c < 3 ? grad + (int64_t)3 * c * n : pgrad;
-            const int64_t vi = c < 3 ? (int64_t)c * n + l : l;
-            GradCoef<float> q;
-            int ih[3];
-            if (!grad_geo(g, c, p, q, ih)) {
-                raise_error(err, l, isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]) ? MLS_E_SUPPORT
-                                                                                          : MLS_E_NONFINITE);
-                const float nan = __builtin_nanf("");
-                if (vo) vo[vi] = nan;
-                if (go) { go[l] = nan; go[n + l] = nan; go[2 * n + l] = nan; }
-                continue;
+        float s[3][3], rH[3];
+        int ih[3] = {1, 0, 0};
+        bool ok = true;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            AxisGeo G;
+            double r;
+            ok = ok && axis_geo(g.ax[d], d == c, p[d], G, r);
+            if (ok) {
+                s[d][0] = G.s[0]; s[d][1] = G.s[1]; s[d][2] = G.s[2];
+                rH[d] = (float)r;
+                ih[d] = G.ih;
             }
-            const int nx = comp_dim(g, c, 0), ny = comp_dim(g, c, 1), nz = comp_dim(g, c, 2);
-            uint32_t oy[3], oz[3];
-            support_rows(true, ih[1], ih[2], nx, ny, nz, g.ax[1].periodic, g.ax[2].periodic, oy, oz);
-            // the 27 field values are requested before the solve, which hides
-            // their latency
-            float qv[kNe];
-            load_support(fq, ih[0], nx, oy, oz, qv);
-            float acc = 0.f, ga[3] = {0.f, 0.f, 0.f};
-            if (grad_coef(Wt, tau, q, kmax)) {
-                // sum_k dphi_dk = 0, so the gradient is summed over q_k - q_home:
-                // the terms are O(h |grad q|) instead of O(|q|), which spares
-                // FP32 the cancellation of an O(|q|/h) sum down to O(|grad q|)
-                const float fh = qv[13];
-                for_each_node<false>(q, Wt, [&](int a, int b, int cz, float ph, const float dv[3]) {
-                    const float fv = qv[a + 3 * b + 9 * cz];
-                    const float df = fv - fh;
-                    acc += ph * fv;
-                    ga[0] += dv[0] * df; ga[1] += dv[1] * df; ga[2] += dv[2] * df;
-                });
-            } else {
-                ++routed;
-                enqueue(queue, l, c);
-                continue;   // the FP64 kernel writes this (marker, staggering)
-            }
-            if (vo) vo[vi] = acc;
-            if (go) { go[l] = ga[0]; go[n + l] = ga[1]; go[2 * n + l] = ga[2]; }
         }
+        if (!ok) {
+            raise_error(err, l, isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]) ? MLS_E_SUPPORT
+                                                                                      : MLS_E_NONFINITE);
+            const float nan = __builtin_nanf("");
+            if (vo) vo[l] = nan;
+            if (go) { go[l] = nan; go[n + l] = nan; go[2 * n + l] = nan; }
+            continue;
+        }
+        uint32_t oy[3], oz[3];
+        support_rows(true, ih[1], ih[2], nx, ny, nz, g.ax[1].periodic, g.ax[2].periodic, oy, oz);
+        // the 27 field values are requested before the solve, which hides
+        // their latency
+        float qv[kNe];
+        load_support(fq, ih[0], nx, oy, oz, qv);
+        float o[4] = {0.f, 0.f, 0.f, 0.f};
+        const bool fp32 = value_and_grad(Wt, tau, s, rH, qv, o, kmax);
+        if (!fp32) ++routed;
+        const bool finite = fabsf(o[0]) <= 3.0e38f && fabsf(o[1]) <= 3.0e38f && fabsf(o[2]) <= 3.0e38f &&
+                            fabsf(o[3]) <= 3.0e38f;
+        // the second kernel writes what is queued
+        enqueue(queue, !fp32 || !finite, (uint32_t)(4 * l + c) | (fp32 ? kDirect : 0u));
+        if (vo) vo[l] = o[0];
+        if (go) { go[l] = o[1]; go[n + l] = o[2]; go[2 * n + l] = o[3]; }
     }
     count_fp64(stats, routed);
 }
@@ -330,12 +463,12 @@ k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, cons
 __global__ void __launch_bounds__(kGradBlock)
 k_build_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const float *__restrict__ x,
                   const float *__restrict__ y, const float *__restrict__ z, float *__restrict__ phi,
-                  float *__restrict__ dphi, const uint32_t *__restrict__ queue, ErrWord *err)
+                  float *__restrict__ dphi, uint32_t *queue, ErrWord *err)
 {
     const Grid &g = *gp;
     const uint32_t cnt = queue[0];
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
-        const uint32_t e = queue[1 + i];
+        const uint32_t e = queue[kQueueHead + i];
         const int64_t l = e >> 2;
         const int c = (int)(e & 3u);
         if (l >= n) continue;
@@ -344,6 +477,7 @@ k_build_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const float
                              dphi + b * 3 * kNe * kLanes + r))
             raise_error(err, l, MLS_E_SINGULAR);
     }
+    queue_done(queue, cnt);
 }
 
 __global__ void __launch_bounds__(kGradBlock)
@@ -351,13 +485,13 @@ k_interp_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const floa
                    const float *__restrict__ y, const float *__restrict__ z, const float *__restrict__ u,
                    const float *__restrict__ v, const float *__restrict__ w, const float *__restrict__ pf,
                    float *__restrict__ val, float *__restrict__ grad, float *__restrict__ pval,
-                   float *__restrict__ pgrad, const uint32_t *__restrict__ queue, ErrWord *err)
+                   float *__restrict__ pgrad, uint32_t *queue, float tau, ErrWord *err)
 {
     const Grid &g = *gp;
     const uint32_t cnt = queue[0];
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
-        const uint32_t e = queue[1 + i];
-        const int64_t l = e >> 2;
+        const uint32_t e = queue[kQueueHead + i];
+        const int64_t l = (e & ~kDirect) >> 2;
         const int c = (int)(e & 3u);
         if (l >= n) continue;
         const double p[3] = {(double)x[l], (double)y[l], (double)z[l]};
@@ -378,12 +512,14 @@ k_interp_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const floa
         }
         const float *fq = c == 0 ? u : (c == 1 ? v : (c == 2 ? w : pf));
         float o4[4];
-        if (!interp_grad_fp64(g, Wt, c, p[0], p[1], p[2], fq, ox, oy, oz, o4)) raise_error(err, l, MLS_E_SINGULAR);
+        if (e & kDirect) interp_grad_direct(g, Wt, tau, c, p, fq, ox, oy, oz, o4);
+        else if (!interp_grad_fp64(g, Wt, c, p[0], p[1], p[2], fq, ox, oy, oz, o4)) raise_error(err, l, MLS_E_SINGULAR);
         float *vo = c < 3 ? val : pval;
         float *go = c < 3 ? grad + (int64_t)3 * c * n : pgrad;
         if (vo) vo[c < 3 ? (int64_t)c * n + l : l] = o4[0];
         if (go) { go[l] = o4[1]; go[n + l] = o4[2]; go[2 * n + l] = o4[3]; }
     }
+    queue_done(queue, cnt);
 }
 
 unsigned grad_blocks(const Ctx &c, int64_t work)
@@ -395,10 +531,10 @@ unsigned grad_blocks(const Ctx &c, int64_t work)
 
 }  // namespace
 
-// The FP64 queue holds up to 4 n entries (one per marker and staggering).
+// The queue holds up to 4 n entries (one per marker and staggering).
 static hipError_t reserve_queue(Ctx &c, int64_t n, hipStream_t s)
 {
-    const int64_t need = 1 + 4 * n;
+    const int64_t need = kQueueHead + 4 * n;
     if (need <= c.grad_queue_cap) return hipSuccess;
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
@@ -408,7 +544,8 @@ static hipError_t reserve_queue(Ctx &c, int64_t n, hipStream_t s)
     e = hipMalloc((void **)&c.grad_queue, (size_t)need * sizeof(uint32_t));
     if (e != hipSuccess) return e;
     c.grad_queue_cap = need;
-    return hipSuccess;
+    hipLaunchKernelGGL(k_queue_clear, dim3(1), dim3(64), 0, s, c.grad_queue);
+    return hipGetLastError();
 }
 
 hipError_t launch_build_grad(Ctx &c, int64_t n, const float *x, const float *y, const float *z, int stagger,
@@ -418,7 +555,6 @@ hipError_t launch_build_grad(Ctx &c, int64_t n, const float *x, const float *y, 
     hipError_t e = reserve_queue(c, n, s);
     if (e != hipSuccess) return e;
     const int64_t npad = (n + kLanes - 1) / kLanes * kLanes;
-    hipLaunchKernelGGL(k_queue_clear, dim3(1), dim3(64), 0, s, c.grad_queue);
     hipLaunchKernelGGL(k_build_grad, dim3(grad_blocks(c, npad)), dim3(kGradBlock), 0, s, c.d_grid, c.w,
                        (float)c.opts.kappa_tau, stagger, n, x, y, z, home, phi, dphi, c.grad_queue, c.err, c.stats);
     hipLaunchKernelGGL(k_build_grad_fp64, dim3(round_up8(c.cu_count)), dim3(kGradBlock), 0, s, c.d_grid, c.w, n, x, y,
@@ -433,11 +569,19 @@ hipError_t launch_interp_grad(Ctx &c, int64_t n, const float *x, const float *y,
     if (n == 0) return hipSuccess;
     hipError_t e = reserve_queue(c, n, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_queue_clear, dim3(1), dim3(64), 0, s, c.grad_queue);
-    hipLaunchKernelGGL(k_interp_grad, dim3(grad_blocks(c, n)), dim3(kGradBlock), 0, s, c.d_grid, c.w,
-                       (float)c.opts.kappa_tau, n, x, y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err, c.stats);
+    // three or four wavefronts per 64 markers, a multiple of 24 workgroups (8 XCDs)
+    const int nc = p ? 4 : 3;
+    int64_t blocks = ((n + 63) / 64 * nc + kGradBlock / 64 - 1) / (kGradBlock / 64);
+    blocks = std::min(blocks, (int64_t)c.cu_count * 32);
+    const dim3 grid((unsigned)((blocks + kBuildGridMultiple - 1) / kBuildGridMultiple * kBuildGridMultiple));
+    if (p)
+        hipLaunchKernelGGL(k_interp_grad<4>, grid, dim3(kGradBlock), 0, s, c.d_grid, c.w, (float)c.opts.kappa_tau, n, x,
+                           y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err, c.stats);
+    else
+        hipLaunchKernelGGL(k_interp_grad<3>, grid, dim3(kGradBlock), 0, s, c.d_grid, c.w, (float)c.opts.kappa_tau, n, x,
+                           y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err, c.stats);
     hipLaunchKernelGGL(k_interp_grad_fp64, dim3(round_up8(c.cu_count)), dim3(kGradBlock), 0, s, c.d_grid, c.w, n, x,
-                       y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err);
+                       y, z, u, v, w, p, U, G, P, GP, c.grad_queue, (float)c.opts.kappa_tau, c.err);
     return hipGetLastError();
 }
 
