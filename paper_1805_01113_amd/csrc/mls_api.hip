@@ -335,12 +335,13 @@ mls_status mls_ctx_create(mls_ctx **out, const mls_grid *grid, const mls_weight 
         a.t_scale = (float)a.inv_h;
         a.t_eps = 1.0f;
         if (a.uniform) {
-            // rounding of f0 and of the difference, of 1/h and of the product,
-            // and how far the faces lie from f0 + i h
+            // rounding of f0 and of the difference, of 1/h, of the product and
+            // of the half added for face nodes, and how far the faces lie from
+            // f0 + i h
             const double ulp = 5.9604644775390625e-8;   // 2^-24
             double dev = 0.0;
             for (int i = 0; i <= n; ++i) dev = std::max(dev, std::fabs(f[i] - (a.f0 + i * (a.L / n))));
-            const double eps = 1.01 * ulp * (std::fabs(a.f0) * a.inv_h + 3.0 * n) + dev * a.inv_h + 1e-6;
+            const double eps = 1.01 * ulp * (std::fabs(a.f0) * a.inv_h + 4.0 * n) + dev * a.inv_h + 1e-6;
             if (eps < 0.25) a.t_eps = (float)eps;
         }
         a.nbucket = 4 * n;

@@ -159,15 +159,26 @@ __device__ __forceinline__ bool cell_axis_f(const Axis &a, float x, int &i)
 // may return n, node 0 shifted by L) and X the wrapped coordinate.
 __device__ __forceinline__ bool locate(const Axis &a, int is_face, double x, int &ih_u, double &X)
 {
-    if (!isfinite(x)) return false;
     const int n = a.n;
+    int i;
+    // as in cell_axis_f: coordinates (FP32 values all of them) away from the
+    // borders of the control volumes
+    const float t = ((float)x - a.t_off) * a.t_scale, ts = is_face ? t + 0.5f : t;
+    const float fl = floorf(ts), fr = ts - fl;
+    if (fr > a.t_eps && fr < 1.0f - a.t_eps && t > 0.0f && t < (float)n) {
+        i = (int)fl;
+        X = x;
+        if (!a.periodic && (i < 1 || i + 1 > (is_face ? n : n - 1))) return false;
+        ih_u = i;
+        return true;
+    }
+    if (!isfinite(x)) return false;
     if (a.periodic) {
         X = wrap_x(a, x);
     } else {
         X = x;
         if (!(X >= fval(a, 0) && X <= fval(a, n))) return false;
     }
-    int i;
     if (!is_face) {
         if (X >= fval(a, n)) return false;
         i = a.uniform ? fix_cell(a, X, min(max((int)floor((X - a.f0) * a.inv_h), 0), n - 1)) : search_cell(a, X);

@@ -32,7 +32,7 @@ def test_fp32_cell_of_a_uniform_axis(n, length, origin):
     L = f[-1] - f[0]
     inv_h = n / L
     dev = np.abs(f - (f[0] + np.arange(n + 1) * (L / n))).max()
-    eps = 1.01 * ULP * (abs(f[0]) * inv_h + 3.0 * n) + dev * inv_h + 1e-6
+    eps = 1.01 * ULP * (abs(f[0]) * inv_h + 4.0 * n) + dev * inv_h + 1e-6
     x = _near(r, f, 200000)
     t = (x - np.float32(f[0])) * np.float32(inv_h)
     fr = t - np.floor(t)
@@ -40,6 +40,12 @@ def test_fp32_cell_of_a_uniform_axis(n, length, origin):
     sure = (fr > e) & (fr < np.float32(1.0) - e) & (t > 0) & (t < n)
     cell = np.searchsorted(f, x.astype(np.float64), side="right") - 1
     assert np.array_equal(np.floor(t[sure]).astype(np.int64), cell[sure])
+    # face nodes: centres[i - 1] <= x < centres[i]
+    th = t + np.float32(0.5)
+    fr = th - np.floor(th)
+    sf = (fr > e) & (fr < np.float32(1.0) - e) & (t > 0) & (t < n)
+    node = np.searchsorted(0.5 * (f[:-1] + f[1:]), x.astype(np.float64), side="right")
+    assert np.array_equal(np.floor(th[sf]).astype(np.int64), node[sf])
     if eps < 0.01:      # a shortcut: nearly every coordinate away from the faces takes it
         assert sure[:200000].mean() > 0.95
 
