@@ -135,7 +135,7 @@ k_build_interp(const Grid *__restrict__ gp, const Weight W, float tau, int64_t n
     // every path through the loop issues the same memory operations: a lane
     // past the end repeats the last marker (writing identical values, its
     // shape function into a padding row) and a marker without a support is
-    // computed on a neutral stencil at node 0 and stored as NaN.  A branch
+    // computed on a neutral stencil at node 1 and stored as NaN.  A branch
     // around stores would make the compiler wait for all of them before the
     // next item's operands.
     const int64_t last = n - 1;
@@ -162,9 +162,9 @@ k_build_interp(const Grid *__restrict__ gp, const Weight W, float tau, int64_t n
         // the 27 field values are requested before the solve, which hides
         // their latency
         uint32_t oy[3], oz[3];
-        support_rows(ok, G[1].ih, G[2].ih, nxc, nyc, nzc, g.ax[1].periodic, g.ax[2].periodic, oy, oz);
-        Support sp;
-        load_support(q, ok ? G[0].ih : 1, nxc, oy, oz, sp);
+        support_rows(G[1].ih, G[2].ih, nxc, nyc, nzc, oy, oz);
+        float qv[kNe];
+        load_rows(q, G[0].ih, nxc, oy, oz, qv);
         const float vbv = vb ? vb[c * n + m] : 0.0f;
         float ph[kNe];
         float gam[4] = {0.f, 0.f, 0.f, 0.f};
@@ -193,9 +193,10 @@ k_build_interp(const Grid *__restrict__ gp, const Weight W, float tau, int64_t n
                     rq[1 + slot + __popcll(rmask & ((1ull << lane) - 1ull))] = (uint32_t)((base + lane) << 2) | c;
             }
         }
+        wrap_rows(q, G[0].ih, G[1].ih, G[2].ih, nxc, nyc, nzc, qv);
         float acc = 0.f;
 #pragma unroll
-        for (int k = 0; k < kNe; ++k) acc += ph[k] * sp.at(k);
+        for (int k = 0; k < kNe; ++k) acc += ph[k] * qv[k];
         const float f = (vbv - acc) * inv_dt;
         st_stream(&U[c * n + m], ok ? acc : nan);
         st_stream(&F[c * n + m], ok ? f : nan);
@@ -459,9 +460,10 @@ k_build_fast(const Grid *__restrict__ gp, const FastTables T, int64_t n,
 // in LDS.  The sub-cell and the weights (Shepard of eq. 10, or trilinear) are
 // those of the whole-table lookup; a corner in the negative half of an axis
 // reads the row of its mirror image, and the blended nodes of every such axis
-// are put back in place with a layer of conditional swaps.
+// are put back in place with a layer of conditional swaps.  Three wavefronts
+// per SIMD: with four the kernel spills (207 -> 200 us on 1.28 M markers).
 template <bool TRILINEAR>
-__global__ void __launch_bounds__(kBuildBlock) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(kBuildBlock) __attribute__((amdgpu_waves_per_eu(3)))
 k_fast_interp(const Grid *__restrict__ gp, const float4 *__restrict__ tab, int nsub, int64_t n,
               const uint32_t *__restrict__ order, const float *__restrict__ x, const float *__restrict__ y,
               const float *__restrict__ z, uint32_t *__restrict__ home, float *__restrict__ phi,
@@ -515,9 +517,10 @@ k_fast_interp(const Grid *__restrict__ gp, const float4 *__restrict__ tab, int n
         neutral_geo_unless(ok, G);
         st_stream(hout, ok ? pack_home(G[0].ih, G[1].ih, G[2].ih) : 0xffffffffu);
         uint32_t oy[3], oz[3];
-        support_rows(ok, G[1].ih, G[2].ih, nxc, nyc, nzc, g.ax[1].periodic, g.ax[2].periodic, oy, oz);
+        support_rows(G[1].ih, G[2].ih, nxc, nyc, nzc, oy, oz);
         float qv[kNe];
-        load_support(q, ok ? G[0].ih : 1, nxc, oy, oz, qv);
+        load_rows(q, G[0].ih, nxc, oy, oz, qv);
+        wrap_rows(q, G[0].ih, G[1].ih, G[2].ih, nxc, nyc, nzc, qv);   // (later, the blend's registers spill)
         const float vbv = vb ? vb[c * n + m] : 0.0f;
         // the sub-cell and the blend weights in the true frame, as the
         // whole-table lookup computes them (so a marker on a sub-cell face

@@ -325,13 +325,13 @@ __device__ __forceinline__ double weight1_d(const Weight &w, double s)
 // Weight and its derivative dw/ds (0 where the shifted Gaussian is clipped).
 __device__ __forceinline__ void weight1_ds(const Weight &w, float s, float &v, float &dv)
 {
-    if (w.kind == MLS_W_CONST) { v = 1.0f; dv = 0.0f; return; }
+    // (cut is 0 for the plain Gaussian; selects, so that a support's nine
+    // evaluations stay in one block)
     const float t = s * w.inv_eps;
     const float g = __expf(-t * t);
     const float dg = -2.0f * t * w.inv_eps * g;
-    if (w.kind == MLS_W_GAUSS) { v = g; dv = dg; return; }
-    v = fmaxf(g - w.cut, 0.0f);
-    dv = g - w.cut > 0.0f ? dg : 0.0f;
+    v = w.kind == MLS_W_CONST ? 1.0f : fmaxf(g - w.cut, 0.0f);
+    dv = w.kind == MLS_W_CONST || !(g - w.cut > 0.0f) ? 0.0f : dg;
 }
 
 __device__ __forceinline__ void weight1_ds(const Weight &w, double s, double &v, double &dv)
@@ -374,7 +374,9 @@ __device__ __forceinline__ void assemble(const Moments<T> mx, const Moments<T> m
 // Cholesky factor of the symmetric 4x4 A (10 entries).  Returns false if A is
 // not numerically positive definite.  L stored row-wise lower: l00 l10 l11
 // l20 l21 l22 l30 l31 l32 l33; the diagonal holds 1/l_ii.
-__device__ __forceinline__ float rsqrt_t(float v) { return rsqrtf(v); }
+// (the instruction itself: a denormal pivot, which rsqrtf would rescale, belongs
+// to a matrix that is far beyond the FP32 condition bound anyway)
+__device__ __forceinline__ float rsqrt_t(float v) { return __builtin_amdgcn_rsqf(v); }
 __device__ __forceinline__ double rsqrt_t(double v) { return 1.0 / sqrt(v); }
 
 template <typename T>
@@ -555,82 +557,40 @@ __device__ __forceinline__ int nb_index(int i, int a, int n, int periodic)
 }
 
 // Node offsets of the three y rows (oy) and z layers (oz) of the support of
-// home (., j, k) on a component grid of nx x ny x nz nodes; zero when ok is
-// false (a lane without a support, which loads row 0).  The grid limits (at
-// most 2048 x 2048 x 1024 nodes per component) keep every node index below
-// 2^32 and nx ny at most 2^22, so the offsets are exact 24-bit products in
-// 32 bits (full-rate multiplies instead of 64-bit ones).
-__device__ __forceinline__ void support_rows(bool ok, int j, int k, int nx, int ny, int nz, int py, int pz,
-                                             uint32_t oy[3], uint32_t oz[3])
+// home (., j, k) on a component grid of nx x ny x nz nodes.  On a wall axis a
+// home is never an end node, so only periodic axes wrap here.  The grid limits
+// (at most 2048 x 2048 x 1024 nodes per component) keep every node index below
+// 2^32 and nx ny at most 2^22, so the offsets are exact in 32 bits (24-bit
+// multiplies at full rate instead of 64-bit ones).
+__device__ __forceinline__ void support_rows(int j, int k, int nx, int ny, int nz, uint32_t oy[3], uint32_t oz[3])
 {
     const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        oy[a] = ok ? __umul24((uint32_t)nb_index(j, a - 1, ny, py), (uint32_t)nx) : 0u;
-        oz[a] = ok ? __umul24((uint32_t)nb_index(k, a - 1, nz, pz), nxy) : 0u;
-    }
+    const uint32_t top_y = nxy - (uint32_t)nx, top_z = nxy * (uint32_t)(nz - 1);
+    oy[1] = __umul24((uint32_t)j, (uint32_t)nx);
+    oy[0] = oy[1] + (j == 0 ? top_y : 0u - (uint32_t)nx);
+    oy[2] = oy[1] + (j == ny - 1 ? 0u - top_y : (uint32_t)nx);
+    oz[1] = __umul24((uint32_t)k, nxy);
+    oz[0] = oz[1] + (k == 0 ? top_z : 0u - nxy);
+    oz[2] = oz[1] + (k == nz - 1 ? 0u - top_z : nxy);
 }
 
-// The 27 values of a field on the support of a home node, as loaded by
-// load_support: v holds the window of each row, e the far end of the row for
-// a stencil that wraps round a periodic x axis.  at(k) is the value of node
-// k = a + 3 b + 9 cz.
-struct Support {
-    float v[kNe];
-    float e[9];
-    bool lo, hi;   // the stencil wraps below node 0 / above node nx - 1
-    __device__ __forceinline__ float at(int k) const
-    {
-        const int r = k / 3, a = k % 3;
-        if (a == 0) return lo ? e[r] : (hi ? v[3 * r + 1] : v[3 * r]);
-        if (a == 1) return lo ? v[3 * r] : (hi ? v[3 * r + 2] : v[3 * r + 1]);
-        return lo ? v[3 * r + 1] : (hi ? e[r] : v[3 * r + 2]);
-    }
-};
-
-// Loads the support values of field q around home node (i, ., .): x index i
-// on rows of length nx >= 3, the rows of the y and z neighbours at offsets
-// oy[b] + oz[cz].  The three x-neighbours of a row arrive in one 12-byte load
-// from the window i - 1 .. i + 1 clamped into the row: a third of the memory
-// instructions of one load per value, which matters because the vector L1
-// serves each instruction cache line by cache line.  A stencil that wraps
-// round a periodic axis (i = 0 or nx - 1) holds two of its values in the
-// window and needs the far end of the row: in a wavefront with such a lane,
-// every lane loads that one extra value per row (elsewhere e stays 0), and
-// Support::at picks each node's value by selects where it is used.  The
-// window registers are never rewritten, so the common path does not wait for
-// the loads before the solve that follows them.  The values are those of one
-// load per node.  A lane without a support passes i = 1 and row offsets 0.
-__device__ __forceinline__ void load_support(const float *__restrict__ q, int i, int nx, const uint32_t oy[3],
-                                             const uint32_t oz[3], Support &sp)
-{
-    const uint32_t sx = (uint32_t)min(max(i - 1, 0), nx - 3);
-    struct Row3 { float v[3]; };
-#pragma unroll
-    for (int r = 0; r < 9; ++r) {
-        Row3 t;
-        __builtin_memcpy(&t, q + (oz[r / 3] + oy[r % 3] + sx), sizeof t);
-        sp.v[3 * r] = t.v[0]; sp.v[3 * r + 1] = t.v[1]; sp.v[3 * r + 2] = t.v[2];
-    }
-    sp.lo = i < 1;
-    sp.hi = i > nx - 2;   // both only on a periodic axis
-#pragma unroll
-    for (int r = 0; r < 9; ++r) sp.e[r] = 0.f;
-    if (__any(sp.lo || sp.hi)) {
-#pragma unroll
-        for (int r = 0; r < 9; ++r) sp.e[r] = q[oz[r / 3] + oy[r % 3] + (sp.lo ? (uint32_t)nx - 1u : 0u)];
-    }
-}
-
-// The same values in a plain array, the wrapping lanes' windows rotated in
-// place by the fix-up.  The compiler then moves the window values into the
-// fix-up's registers on the common path and waits for the loads there, which
-// costs the latency that Support hides, but the array needs 9 registers fewer
-// than Support.  The fused fast-MLS kernel, at its limit of 128 registers, and
-// the velocity-gradient kernel, which uses the values inside its node visitor,
-// are faster this way.
-__device__ __forceinline__ void load_support(const float *__restrict__ q, int i, int nx, const uint32_t oy[3],
-                                             const uint32_t oz[3], float qv[kNe])
+// The support values of field q around home node (i, ., .), qv[a + 3 b + 9 c]:
+// x index i on rows of length nx >= 3, the rows of the y and z neighbours at
+// offsets oy[b] + oz[c].  load_rows requests, for each of the nine rows, the
+// three x-neighbours in one 12-byte load from the window i - 1 .. i + 1 clamped
+// into the row: a third of the memory instructions of one load per value,
+// which matters because the vector L1 serves each instruction cache line by
+// cache line.  A stencil that wraps round a periodic axis (i = 0 or nx - 1)
+// holds two of its values in the window; wrap_rows, in a wavefront with such a
+// lane, loads the far end of each row and rotates those lanes' windows.  The
+// values are those of one load per node.
+// Call wrap_rows where the values are used, after the solve that hides the
+// loads' latency: called at once it waits for them on every path (the fused
+// exact build took 2.53 ms instead of 2.34 on 22.66 M markers), and choosing
+// each node's value by selects instead takes 75 instructions per support on
+// every path (gradients of 2.56 M markers 0.42 ms instead of 0.38).
+__device__ __forceinline__ void load_rows(const float *__restrict__ q, int i, int nx, const uint32_t oy[3],
+                                          const uint32_t oz[3], float qv[kNe])
 {
     const uint32_t sx = (uint32_t)min(max(i - 1, 0), nx - 3);
     struct Row3 { float v[3]; };
@@ -640,8 +600,16 @@ __device__ __forceinline__ void load_support(const float *__restrict__ q, int i,
         __builtin_memcpy(&t, q + (oz[r / 3] + oy[r % 3] + sx), sizeof t);
         qv[3 * r] = t.v[0]; qv[3 * r + 1] = t.v[1]; qv[3 * r + 2] = t.v[2];
     }
+}
+
+__device__ __forceinline__ void wrap_rows(const float *__restrict__ q, int i, int j, int k, int nx, int ny, int nz,
+                                          float qv[kNe])
+{
     const bool lo = i < 1, hi = i > nx - 2;   // only on a periodic axis
     if (__any(lo || hi)) {
+        // (the row offsets again, so that they need not stay in registers)
+        uint32_t oy[3], oz[3];
+        support_rows(j, k, nx, ny, nz, oy, oz);
 #pragma unroll
         for (int r = 0; r < 9; ++r) {
             const float e = q[oz[r / 3] + oy[r % 3] + (lo ? (uint32_t)nx - 1u : 0u)];

@@ -46,7 +46,7 @@ __device__ __forceinline__ bool solve_fp64_regs(const Grid &g, const Weight &W, 
 }
 
 // Stencil for a marker without a support (where ok is false): the uniform
-// node offsets -1, 0, 1 at node 0.  The fused kernels compute such a marker
+// node offsets -1, 0, 1 at node 1, whose neighbours every axis has.  The fused kernels compute such a marker
 // like any other (so all lanes issue the same memory operations) and store
 // NaN in its place.  Selects on every field (G may hold anything there), so
 // that the compiler does not first set every register to the neutral values
@@ -55,7 +55,7 @@ __device__ __forceinline__ void neutral_geo_unless(bool ok, AxisGeo G[3])
 {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        G[d].ih = ok ? G[d].ih : 0;
+        G[d].ih = ok ? G[d].ih : 1;
         G[d].s[0] = ok ? G[d].s[0] : -1.f;
         G[d].s[1] = ok ? G[d].s[1] : 0.f;
         G[d].s[2] = ok ? G[d].s[2] : 1.f;

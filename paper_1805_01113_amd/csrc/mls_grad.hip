@@ -320,8 +320,10 @@ k_build_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int c, int64_t n
 // are products of three axes, so the 16 sums are contracted axis by axis: 237
 // multiply-adds for the 27 nodes, where visiting each node takes about 950
 // operations.  Returns false if the pair goes to FP64.
+// wrap() puts the values of wrapping stencils in place, once they are needed.
+template <typename F>
 __device__ __forceinline__ bool value_and_grad(const Weight &Wt, float tau, const float s[3][3], const float rH[3],
-                                               const float qv[kNe], float out[4], float &kmax)
+                                               const float (&qv)[kNe], F &&wrap, float out[4], float &kmax)
 {
     // per axis and node: w, w s, -w', -w' s (the factors of W_k p_k and dW_dk p_k)
     float w0[3][3], w1[3][3], d0[3][3], d1[3][3];
@@ -345,10 +347,14 @@ __device__ __forceinline__ bool value_and_grad(const Weight &Wt, float tau, cons
     }
     float A[10], L[10], gam[4];
     assemble(m[0], m[1], m[2], A);
-    if (!cholesky4(A, L)) return false;
-    const float kap = cond_bound_and_gamma(A, L, gam);
-    kmax = fmaxf(kmax, isfinite(kap) ? kap : 3.0e38f);
-    if (!(kap <= tau)) return false;
+    bool ok = cholesky4(A, L);
+    if (ok) {
+        const float kap = cond_bound_and_gamma(A, L, gam);
+        kmax = fmaxf(kmax, isfinite(kap) ? kap : 3.0e38f);
+        ok = kap <= tau;
+    }
+    wrap();   // (votes over the wavefront: every lane comes here)
+    if (!ok) return false;
     // x, then y, then z: names give the factor kind per axis (0: w, 1: w s, 2: -w', 3: -w' s)
     const float fh = qv[13];
     float T[4] = {0.f, 0.f, 0.f, 0.f}, Tx[4] = {0.f, 0.f, 0.f, 0.f}, Ty[4] = {0.f, 0.f, 0.f, 0.f},
@@ -441,13 +447,13 @@ k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, cons
             continue;
         }
         uint32_t oy[3], oz[3];
-        support_rows(true, ih[1], ih[2], nx, ny, nz, g.ax[1].periodic, g.ax[2].periodic, oy, oz);
+        support_rows(ih[1], ih[2], nx, ny, nz, oy, oz);
         // the 27 field values are requested before the solve, which hides
         // their latency
         float qv[kNe];
-        load_support(fq, ih[0], nx, oy, oz, qv);
+        load_rows(fq, ih[0], nx, oy, oz, qv);
         float o[4] = {0.f, 0.f, 0.f, 0.f};
-        const bool fp32 = value_and_grad(Wt, tau, s, rH, qv, o, kmax);
+        const bool fp32 = value_and_grad(Wt, tau, s, rH, qv, [&]() { wrap_rows(fq, ih[0], ih[1], ih[2], nx, ny, nz, qv); }, o, kmax);
         if (!fp32) ++routed;
         const bool finite = fabsf(o[0]) <= 3.0e38f && fabsf(o[1]) <= 3.0e38f && fabsf(o[2]) <= 3.0e38f &&
                             fabsf(o[3]) <= 3.0e38f;

@@ -889,16 +889,16 @@ k_build_learned(const Grid *__restrict__ gp, const Weight W, float tau, float to
                 unpack_home(hv, i, j, k);
                 const float *q = c == 0 ? li.u : (c == 1 ? li.v : li.w);
                 uint32_t oy[3], oz[3];
-                support_rows(true, j, k, g.dims[c][0], g.dims[c][1], g.dims[c][2], g.ax[1].periodic,
-                             g.ax[2].periodic, oy, oz);
-                Support sp;
-                load_support(q, i, g.dims[c][0], oy, oz, sp);
+                support_rows(j, k, g.dims[c][0], g.dims[c][1], g.dims[c][2], oy, oz);
+                float qv[kNe];
+                load_rows(q, i, g.dims[c][0], oy, oz, qv);
                 float ph[kNe];
 #pragma unroll
                 for (int kk = 0; kk < kNe; ++kk) ph[kk] = stage[kk * 64 + lane];
+                wrap_rows(q, i, j, k, g.dims[c][0], g.dims[c][1], g.dims[c][2], qv);
                 acc = 0.0f;
 #pragma unroll
-                for (int kk = 0; kk < kNe; ++kk) acc += ph[kk] * sp.at(kk);
+                for (int kk = 0; kk < kNe; ++kk) acc += ph[kk] * qv[kk];
                 const float vbv = li.vb ? li.vb[c * n + mk] : 0.0f;
                 fo = (vbv - acc) * li.inv_dt;
                 cfv = eq8_coef_built(g, c, i, j, k, ph, li.area[mk] * fo);

@@ -47,14 +47,17 @@ k_interp(const Grid *__restrict__ gp, int64_t n, const uint32_t *__restrict__ ho
                 continue;
             }
             uint32_t oy[3], oz[3];
-            support_rows(true, j, k, g.dims[c][0], g.dims[c][1], g.dims[c][2], g.ax[1].periodic, g.ax[2].periodic,
-                         oy, oz);
-            Support sp;
-            load_support(q, i, g.dims[c][0], oy, oz, sp);
+            support_rows(j, k, g.dims[c][0], g.dims[c][1], g.dims[c][2], oy, oz);
+            float qv[kNe];
+            load_rows(q, i, g.dims[c][0], oy, oz, qv);
             const float *p = phi + phi_at(l, c);
+            float ph[kNe];
+#pragma unroll
+            for (int kk = 0; kk < kNe; ++kk) ph[kk] = p[kk * kLanes];
+            wrap_rows(q, i, j, k, g.dims[c][0], g.dims[c][1], g.dims[c][2], qv);
             float acc = 0.f;
 #pragma unroll
-            for (int kk = 0; kk < kNe; ++kk) acc += p[kk * kLanes] * sp.at(kk);
+            for (int kk = 0; kk < kNe; ++kk) acc += ph[kk] * qv[kk];
             out[l] = acc;
         }
     }
