@@ -6,19 +6,21 @@
 // The paper fills the array in one sequential sweep (an empty cell takes the
 // body id, a cell holding another id becomes -1).  Its final state does not
 // depend on the order of the sweep: -1 exactly where two or more bodies meet,
-// else the one body's id.  Here that state is reached without an atomic, in two
-// launches: in the first every marker of an empty cell stores its id, and one
-// that sees another body's id stores -1; whichever store lasts, the cell then
-// holds one of its bodies' ids or -1.  In the second every marker whose cell
-// holds neither its own id nor -1 stores -1, the only value stored there, so a
-// cell of several bodies ends at -1 (all but one body see a foreign id) and a
-// cell of one body keeps its id, bit for bit on any schedule.
+// else the one body's id.  So markers enter their ids in parallel: a
+// compare-and-swap puts the id into an empty cell, and where it finds another
+// body's id, -1 replaces it.  The result is the same bit for bit on any schedule.
+// (Plain stores, settled by a second pass, lose ids now and then: a cell that
+// markers on two XCDs write at once can look different to each of them even in
+// the next launch.)
 //
-// Bound by memory: a pass reads 12-16 B per marker and about 19 B of its cells'
-// 128-byte lines (surfaces fill them sparsely), the first also writes those.
-// 22.4 M markers in 1024^3: 0.24 and 0.19 ms for the two launches, 5 TB/s;
-// entering with a compare-and-swap per marker, which the memory side executes,
-// took 0.75 ms.  Four markers a thread at a time change nothing.
+// Entering is bound by the compare-and-swaps, which the memory side executes:
+// 0.56 ms for 22.4 M markers in 1024^3 beyond the pass over them when every
+// marker made one whose cell did not yet show its id.  About two thirds of the
+// markers share a cell with another of their body that the same workgroup
+// handles, so the workgroup keeps the (cell, body) pairs it has entered in LDS
+// and makes one per cell: 0.75 -> 0.26 ms.  Marking (0.16 ms) and clearing
+// (0.17 ms) read 12 B per marker and about 19 B of its cells' 128-byte lines
+// (surfaces fill them sparsely), 4 to 5 TB/s.
 #include "mls_device.h"
 
 namespace mls {
@@ -26,6 +28,9 @@ namespace mls {
 namespace {
 
 constexpr int kCollBlock = 256;
+// 2^kEnteredBits pairs (8 KB); 2^9 to 2^11 take the same time, 2^12 leaves too
+// few workgroups per compute unit (collide and clear 0.59 -> 0.73 ms).
+constexpr int kEnteredBits = 10;
 
 // Linear index [z][y][x] of the cell of marker l, or -1 (error raised, if err is given).
 __device__ __forceinline__ int64_t marker_cell(const Grid &g, int64_t l, const float *x, const float *y,
@@ -39,16 +44,23 @@ __device__ __forceinline__ int64_t marker_cell(const Grid &g, int64_t l, const f
     return ((int64_t)k * g.ax[1].n + j) * g.ax[0].n + i;
 }
 
-// First launch: ids into empty cells, -1 where another body's id is seen.  A
-// body id out of range is left out (reported here).
+// Ids into the cells.  A body id out of range is left out (reported here).
+// entered holds (cell, body) pairs that the workgroup has entered, by a hash of
+// the cell, the newest in its place: a marker that finds its own pair there is
+// done.
 __global__ void __launch_bounds__(kCollBlock)
 k_coll_enter(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x, const float *__restrict__ y,
              const float *__restrict__ z, const int32_t *__restrict__ body, int32_t *__restrict__ coll,
              ErrWord *err)
 {
+    __shared__ unsigned long long entered[1 << kEnteredBits];
     const Grid &g = *gp;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t l = xcd_block() * blockDim.x + threadIdx.x; l < n; l += stride) {
+    for (int q = threadIdx.x; q < 1 << kEnteredBits; q += kCollBlock) entered[q] = ~0ull;   // no body has id -1
+    __syncthreads();
+    // the workgroup's markers: a contiguous range
+    const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 63) & ~(int64_t)63;
+    const int64_t first = xcd_block() * per, last = min(first + per, n);
+    for (int64_t l = first + threadIdx.x; l < last; l += kCollBlock) {
         const int64_t cell = marker_cell(g, l, x, y, z, err);
         if (cell < 0) continue;
         const int32_t b = body[l];
@@ -56,25 +68,10 @@ k_coll_enter(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x
             raise_error(err, l, MLS_E_ARG);
             continue;
         }
-        const int32_t seen = coll[cell];
-        if (seen == b + 1 || seen == -1) continue;
-        coll[cell] = seen == 0 ? b + 1 : -1;
-    }
-}
-
-// Second launch: -1 where a marker's cell kept another body's id.
-__global__ void __launch_bounds__(kCollBlock)
-k_coll_settle(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x, const float *__restrict__ y,
-              const float *__restrict__ z, const int32_t *__restrict__ body, int32_t *__restrict__ coll)
-{
-    const Grid &g = *gp;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t l = xcd_block() * blockDim.x + threadIdx.x; l < n; l += stride) {
-        const int64_t cell = marker_cell(g, l, x, y, z, nullptr);
-        const int32_t b = body[l];
-        if (cell < 0 || b < 0 || b > 2147483646) continue;
-        const int32_t seen = coll[cell];
-        if (seen != b + 1 && seen != -1) coll[cell] = -1;
+        const unsigned long long pair = (unsigned long long)(uint32_t)cell << 32 | (uint32_t)b;
+        if (atomicExch(&entered[((uint32_t)cell * 2654435761u) >> (32 - kEnteredBits)], pair) == pair) continue;
+        const int32_t old = atomicCAS(&coll[cell], 0, b + 1);
+        if (old != 0 && old != b + 1 && old != -1) atomicExch(&coll[cell], -1);
     }
 }
 
@@ -119,7 +116,6 @@ hipError_t launch_collide(const Ctx &c, int64_t n, const float *x, const float *
     if (n == 0) return hipSuccess;
     const unsigned nb = coll_blocks(c, n);
     hipLaunchKernelGGL(k_coll_enter, dim3(nb), dim3(kCollBlock), 0, s, c.d_grid, n, x, y, z, body, coll, c.err);
-    hipLaunchKernelGGL(k_coll_settle, dim3(nb), dim3(kCollBlock), 0, s, c.d_grid, n, x, y, z, body, coll);
     if (flags) hipLaunchKernelGGL(k_coll_mark, dim3(nb), dim3(kCollBlock), 0, s, c.d_grid, n, x, y, z, coll, flags);
     return hipGetLastError();
 }
