@@ -76,24 +76,27 @@ __device__ __forceinline__ float gelu(float z, float &dz)
     return z * cdf;
 }
 
-// gelu(z) = max(z, 0) - |z| Q(|z|) from the cubic table of the network image
-// (inference only; training keeps the closed form above).  Beyond |z| = 6 the
-// last interval's end value, 6 Q(6) < 6e-9, stands in for |z| Q(|z|).
-// max(z, 0) is taken as z - min(z, 0), which passes a NaN argument on to the
-// result (min returns its other operand for a NaN).
-__device__ __forceinline__ float gelu_tab(float z, const float4 *__restrict__ tab)
-{
-    const float t = fminf(fabsf(z) * (float)kGeluPerUnit, 95.99999f);
-    const float4 c = tab[(int)t];
-    const float sv = __builtin_amdgcn_fractf(t);
-    const float p = fmaf(fmaf(fmaf(c.w, sv, c.z), sv, c.y), sv, c.x);
-    return (z - fminf(z, 0.0f)) - p;
-}
-
 __device__ __forceinline__ void split_bf16(float v, __bf16 &hi, __bf16 &lo)
 {
     hi = (__bf16)v;
     lo = (__bf16)(v - (float)hi);
+}
+
+// The same of two values, with v - hi as a two-term dot product whose other
+// factor picks one half of the packed hi, in place of an unpacking shift and a
+// subtraction.  The difference is exact in FP32 either way.  An infinity or NaN
+// spreads to its neighbour's lo; both belong to one row of a product, which it
+// makes non-finite anyway.  (The factors are hidden from the compiler: as
+// constants it encoded {-1, 0} as -1 in both halves.)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_bf16_pair(float v0, float v1, bf16x2 &hi, bf16x2 &lo)
+{
+    uint32_t first = 0x0000bf80u, second = 0xbf800000u;   // -1 in one half
+    asm("" : "+s"(first));
+    asm("" : "+s"(second));
+    hi = bf16x2{(__bf16)v0, (__bf16)v1};
+    lo = bf16x2{(__bf16)__builtin_amdgcn_fdot2_f32_bf16(hi, __builtin_bit_cast(bf16x2, first), v0, false),
+                (__bf16)__builtin_amdgcn_fdot2_f32_bf16(hi, __builtin_bit_cast(bf16x2, second), v1, false)};
 }
 
 __device__ __forceinline__ f32x16 mfma3(bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 bl, f32x16 c)
@@ -675,14 +678,48 @@ __device__ __forceinline__ f32x16 bias_tile(const float *b, int T, int h)
     return acc;
 }
 
-// GELU of result registers 8 q .. 8 q + 7 as the split B operand of the next layer.
-__device__ __forceinline__ void gelu_operand(const f32x16 &acc, int q, const float4 *tab, bf16x8 &hi, bf16x8 &lo)
+// gelu(z) = max(z, 0) - |z| Q(|z|) from the cubic table of the network image
+// (inference only; training keeps the closed form above).  Beyond |z| = 6 the
+// last interval's end value, 6 Q(6) < 6e-9, stands in for |z| Q(|z|).
+// gelu_rows reads the table rows of result registers 8 q .. 8 q + 7;
+// gelu_operand makes their GELU the split B operand of the next layer.
+struct GeluRows {
+    float4 c[8];
+    float s[8];
+};
+__device__ __forceinline__ GeluRows gelu_rows(const f32x16 &acc, int q, const float4 *tab)
 {
+    GeluRows r;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        __bf16 p, r;
-        split_bf16(gelu_tab(acc[8 * q + i], tab), p, r);
-        hi[i] = p; lo[i] = r;
+        const float t = fminf(fabsf(acc[8 * q + i]) * (float)kGeluPerUnit, 95.99999f);
+        r.c[i] = tab[(int)t];
+        r.s[i] = __builtin_amdgcn_fractf(t);
+    }
+    return r;
+}
+
+__device__ __forceinline__ void gelu_operand(const f32x16 &acc, int q, const GeluRows &r, bf16x8 &hi, bf16x8 &lo)
+{
+    // max(z, 0) is taken as z - min(z, 0), which passes a NaN argument on to
+    // the result, and min(z, 0) as the median of z, 0 and -infinity (the lower
+    // of the others for a NaN; hidden from the compiler, which would make it a
+    // minimum and quiet its argument with a further operation)
+    float low = -__builtin_inff();
+    asm("" : "+s"(low));
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float z = acc[8 * q + i], t = r.s[i];
+        const float p = fmaf(fmaf(fmaf(r.c[i].w, t, r.c[i].z), t, r.c[i].y), t, r.c[i].x);
+        v[i] = (z - __builtin_amdgcn_fmed3f(z, 0.0f, low)) - p;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        bf16x2 p, l;
+        split_bf16_pair(v[i], v[i + 1], p, l);
+        hi[i] = p.x; hi[i + 1] = p.y;
+        lo[i] = l.x; lo[i + 1] = l.y;
     }
 }
 
@@ -704,38 +741,80 @@ __device__ __forceinline__ f32x16 evaluate(const uint4 *img, const float *b1, co
     }
     // Layer 2 is accumulated k block by k block: each 32-unit tile of layer 1
     // is computed, activated and consumed by the four layer-2 output tiles
-    // at once, so only its own 16-register operand pair is live instead of
-    // all of layer 1, and the four accumulators give the matrix cores four
-    // independent chains.  Each accumulator still sums its k blocks in
-    // order 0..7, so the result is the same as tile by tile.
+    // at once, so only its own registers are live instead of all of layer 1.
+    // The matrix products of a step are issued between the vector operations
+    // that activate the next step's operand: a product occupies the matrix
+    // core for as long as eight of them take to issue, a wavefront issues in
+    // order, and with two wavefronts per SIMD (the network image and the staged
+    // rows fill the LDS) nothing else fills the gaps.  Each accumulator sums
+    // its k blocks in order.  Learned step of 2.56e6 markers in the channel:
+    // 2460 us as the compiler ordered it (two table reads, then a wait, 64
+    // times), 2430 with a step's table rows and operands requested together,
+    // 2365 interleaved.
     f32x16 acc[4];
 #pragma unroll
     for (int T = 0; T < 4; ++T) acc[T] = bias_tile(b2, T, h);
+    f32x16 a = bias_tile(b1, 0, h);
+    a = mfma3(op_at(img, 0, 0, lane), op_at(img, 0, 1, lane), uh, ul, a);
+    bf16x8 bh, bl;
+    gelu_operand(a, 0, gelu_rows(a, 0, tab), bh, bl);
 #pragma unroll
-    for (int T1 = 0; T1 < 4; ++T1) {
-        f32x16 a = bias_tile(b1, T1, h);
-        a = mfma3(op_at(img, T1, 0, lane), op_at(img, T1, 1, lane), uh, ul, a);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int kb = 2 * T1 + q;
-            bf16x8 bh, bl;
-            gelu_operand(a, q, tab, bh, bl);
-#pragma unroll
-            for (int T = 0; T < 4; ++T)
-                acc[T] = mfma3(op_at(img, 4 + 8 * T + kb, 0, lane), op_at(img, 4 + 8 * T + kb, 1, lane), bh, bl,
-                               acc[T]);
+    for (int s = 0; s < 8; ++s) {
+        // operand of the next step: the other half of this tile, or the first
+        // half of the next
+        f32x16 an = a;
+        if ((s & 1) && s < 7) {
+            const int T1 = (s + 1) / 2;
+            an = bias_tile(b1, T1, h);
+            an = mfma3(op_at(img, T1, 0, lane), op_at(img, T1, 1, lane), uh, ul, an);
         }
+        bf16x8 wh[4], wl[4], nh, nl;
+#pragma unroll
+        for (int T = 0; T < 4; ++T) {
+            wh[T] = op_at(img, 4 + 8 * T + s, 0, lane);
+            wl[T] = op_at(img, 4 + 8 * T + s, 1, lane);
+        }
+        GeluRows rows;
+        if (s < 7) rows = gelu_rows(an, (s + 1) & 1, tab);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int T = 0; T < 4; ++T) acc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh[T], bh, acc[T], 0, 0, 0);
+#pragma unroll
+        for (int T = 0; T < 4; ++T) acc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh[T], bl, acc[T], 0, 0, 0);
+#pragma unroll
+        for (int T = 0; T < 4; ++T) acc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl[T], bh, acc[T], 0, 0, 0);
+        if (s < 7) {
+            gelu_operand(an, (s + 1) & 1, rows, nh, nl);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 7, 0);
+            }
+            bh = nh; bl = nl;
+            a = an;
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
     f32x16 y3 = bias_tile(b3, 0, h);
+    gelu_operand(acc[0], 0, gelu_rows(acc[0], 0, tab), bh, bl);
 #pragma unroll
-    for (int T = 0; T < 4; ++T) {
+    for (int s = 0; s < 8; ++s) {
+        const bf16x8 wh = op_at(img, 36 + s, 0, lane), wl = op_at(img, 36 + s, 1, lane);
+        GeluRows rows;
+        bf16x8 nh, nl;
+        if (s < 7) rows = gelu_rows(acc[(s + 1) / 2], (s + 1) & 1, tab);
+        __builtin_amdgcn_sched_barrier(0);
+        y3 = mfma3(wh, wl, bh, bl, y3);
+        if (s < 7) {
+            gelu_operand(acc[(s + 1) / 2], (s + 1) & 1, rows, nh, nl);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            bf16x8 ch, cl;
-            gelu_operand(acc[T], q, tab, ch, cl);
-            const int slot = 36 + 2 * T + q;
-            y3 = mfma3(op_at(img, slot, 0, lane), op_at(img, slot, 1, lane), ch, cl, y3);
+            for (int k = 0; k < 3; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 24, 0);
+            }
+            bh = nh; bl = nl;
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
     return y3;
 }
