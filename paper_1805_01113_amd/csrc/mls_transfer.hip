@@ -515,13 +515,15 @@ accumulate_rows(const Grid &g, int c, uint32_t beg, uint32_t end, int b0x, int b
     // share nodes: with 64 consecutive rows in a wavefront its atomics meet on
     // the same addresses, which LDS serves one after another (18 cycles an
     // instruction where distinct banks take 9 to 13).  Compact rows are
-    // therefore dealt out to the workgroup's wavefronts in turn: measured
-    // (22.4e6 markers, 1024^3) the whole step went from 4634 to 4452 us,
-    // (2000 spheres in the 512 x 512 x 768 channel, whole step) 901 to 871.  Full rows are read as 27 words
-    // of 64 consecutive rows, of which every wavefront would then use a part
-    // of each line: they stay consecutive (509 us, dealt out 522 to 582).
-    const uint32_t waves = blockDim.x >> 6;
-    const uint32_t e0 = NF > 0 ? (threadIdx.x & 63u) * waves + (threadIdx.x >> 6) : threadIdx.x;
+    // therefore dealt out in turn to the groups of 16 lanes that LDS takes
+    // together.  Whole steps, consecutive / dealt out to the wavefronts / to
+    // groups of 16: 1000 ellipsoids in 512^3 436 / 423 / 416 us, 2000 spheres in
+    // the 512 x 512 x 768 channel 901 / 876 / 864, 22.4e6 markers in 1024^3
+    // 4634 / 4563 / 4525.  Full rows are read as 27 words of 64 consecutive
+    // rows, of which every wavefront would then use a part of each line: they
+    // stay consecutive (509 us, dealt out 522 to 582, permuted within a
+    // wavefront no change).
+    const uint32_t e0 = NF > 0 ? (threadIdx.x & 15u) * (blockDim.x >> 4) + (threadIdx.x >> 4) : threadIdx.x;
     for (uint32_t e = beg + e0; e < end; e += blockDim.x) {
         // tile order: the row is the entry, so no load waits for the
         // marker index (read on the error path only)
