@@ -205,9 +205,15 @@ struct Ctx {
     uint32_t *work = nullptr;          // kWorkWords: active-list sizes per colour and claim cursors
     int64_t colour_tiles[27] = {};     // tiles of each colour
     // launch shapes (autotuned): resident workgroups per compute unit
-    int spread_blocks_per_cu = 16;      // effective (bounded by the LDS of the tile boxes)
-    int spread_blocks_per_cu_req = 16;  // requested
-    int spread_threads = 128;           // threads of a spreading tile workgroup (128, 192 or 256)
+    // 8 workgroups of 192 threads are the 24 wavefronts that a compute unit
+    // holds of k_spread_colour: with more, the first round's last workgroups
+    // start when others end (16 of 128 threads: 1000 ellipsoids in 512^3 413 us
+    // a step against 401, a standalone spreading of 0.67e6 markers 530 against
+    // 512 with its build, 2000 spheres in the channel 868 against 862; 22.4e6
+    // markers in 1024^3 the same within 1 %)
+    int spread_blocks_per_cu = 8;       // effective (bounded by the LDS of the tile boxes)
+    int spread_blocks_per_cu_req = 8;   // requested
+    int spread_threads = 192;           // threads of a spreading tile workgroup (128, 192 or 256)
     int build_blocks_per_cu = 32;
     int interp_blocks_per_cu = 32;
     int cu_count = 256;

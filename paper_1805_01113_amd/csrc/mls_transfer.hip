@@ -662,10 +662,9 @@ accumulate_rows(const Grid &g, int c, uint32_t beg, uint32_t end, int by, int bz
 // builds write them) or by marker (a standalone call: k_spread_coef).  Per tile, the largest finite |c_l F_l|
 // of its rows sets the fixed-point scale of each component.
 // Workgroups of 128, 192 or 256 threads (tuned, at most kSpreadBlock).  A tile
-// holds some 200 rows: when each workgroup handles many tiles, 128 threads
-// leave fewer lanes idle, pay cheaper barriers and keep more tiles in flight
-// per compute unit; when a colour has only a tile or two per workgroup, 256
-// threads finish each tile sooner.
+// holds some 200 rows: fewer threads leave fewer lanes idle, pay cheaper
+// barriers and keep more tiles in flight per compute unit; more finish a tile
+// sooner when a colour has only a tile or two per workgroup.
 // BX > 0: every axis has more than one tile and the box rows hold BX nodes.
 // Then the 27 support nodes of a row are three consecutive nodes on each box
 // axis, so one box address per row serves all 27 atomics (the others are
@@ -688,11 +687,13 @@ k_spread_colour(const Grid *__restrict__ gp, int colour, const uint32_t *__restr
     const int64_t abase = g.colour_base[colour];
     const uint32_t nact = (uint32_t)min((int64_t)work[colour], colour_end(g, colour) - abase);
     __shared__ int64_t unit_sh;
-    // Work units of a launch: a colour with fewer tiles than workgroups is cut
+    // Work units of a launch: a colour with up to three tiles a workgroup is cut
     // into its (tile, component) pairs, so that a tile's three components run
-    // side by side; else a unit is a whole tile.
+    // side by side and the last round is short (2000 spheres in the channel,
+    // 1.1 tiles a workgroup: 840 us a step, whole tiles 946); else a unit is a
+    // whole tile (cut up to eight tiles a workgroup: 862).
     const uint32_t G = gridDim.x;
-    const bool split = nact <= G;
+    const bool split = nact <= 3u * G;
     const uint32_t units = split ? 3u * nact : nact;
     // Workgroup b starts with unit b and ends there if the first round covers
     // all units; further units are claimed.  Atomics on one address are served
