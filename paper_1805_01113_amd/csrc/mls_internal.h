@@ -307,7 +307,6 @@ hipError_t launch_spread(Ctx &c, int64_t n, const uint32_t *home, const float *p
 // indices, markers without a valid support last), the fused build writes row
 // p of home / phi for marker entries[p] together with U, F and per-block
 // force maxima, and the tile kernels read the rows of a tile contiguously.
-int build_blocks(const Ctx &c, int64_t n);   // workgroups of a build launch over n markers
 // Bins the markers by spreading tile from their positions x, y, z; with jx
 // non-NULL the positions are first jittered (amplitude jitter, the step's
 // generator and device counter) into jx, jy, jz, and those are binned.  advance:
