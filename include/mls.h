@@ -519,7 +519,9 @@ mls_status mls_autotune(mls_ctx *ctx, int32_t method, int32_t flags, const mls_s
 #define MLS_MLP_PARAMS 20891
 
 /* Load parameters and normalisation (HOST pointers, copied) and reset the
- * Adam state.  MLS_E_ARG on a non-finite value. */
+ * Adam state.  MLS_E_ARG on a non-finite value.  Synchronises the device;
+ * forward and gradient passes that a caller has captured in a graph read the
+ * parameters loaded last. */
 mls_status mls_mlp_load(mls_ctx *ctx, const float *params, const float *norm);
 
 /* Copy the current parameters (MLS_MLP_PARAMS floats) and normalisation (12)

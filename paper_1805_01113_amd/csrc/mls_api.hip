@@ -781,13 +781,28 @@ mls_status mls_mlp_load(mls_ctx *ctx, const float *params, const float *norm)
         if (!std::isfinite(params[i])) return fail(ctx, MLS_E_ARG, "non-finite network parameter %d", i);
     for (int i = 0; i < 12; ++i)
         if (!std::isfinite(norm[i])) return fail(ctx, MLS_E_ARG, "non-finite input normalisation %d", i);
-    hipError_t e = mlp_alloc(c);
+    // (the packing below is a kernel: it has to run where the context lives)
+    struct OnDevice {
+        int before = -1;
+        ~OnDevice() { if (before >= 0) hipSetDevice(before); }
+    } on;
+    int dev = c.device;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess && dev != c.device) {
+        e = hipSetDevice(c.device);
+        on.before = dev;
+    }
+    if (e == hipSuccess) e = mlp_alloc(c);
     if (e != hipSuccess) return hip_fail(ctx, e, "network allocation");
     if (hipDeviceSynchronize() != hipSuccess) return MLS_E_HIP;
     Mlp &net = c.mlp;
     e = hipMemcpy(net.params, params, kMlpParams * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(net.norm, norm, 12 * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(net.m1, 0, 2 * (size_t)kMlpParams * sizeof(float));
+    // packed here, not by the next pass: a pass that a caller has captured
+    // reads the same image again
+    if (e == hipSuccess) e = mlp_pack_train(c, nullptr);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(ctx, e, "network upload");
     memcpy(net.h_norm, norm, sizeof(net.h_norm));
     net.adam_step = 0;

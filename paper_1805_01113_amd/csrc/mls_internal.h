@@ -154,7 +154,7 @@ struct Mlp {
     void *train_image = nullptr;   // the weights as operands of the training kernels
     float *loss = nullptr;     // 1 (device)
     float h_norm[12] = {};
-    int64_t version = 0, image_version = -1, train_version = -1;
+    int64_t version = 0, image_version = -1;
     int64_t adam_step = 0;
     float *scratch = nullptr;  // training activations
     int64_t cap_batch = 0;
@@ -356,6 +356,7 @@ hipError_t mlp_alloc(Ctx &c);
 void mlp_free(Ctx &c);
 hipError_t mlp_reserve(Ctx &c, int64_t batch);
 hipError_t mlp_pack(Ctx &c, hipStream_t s);
+hipError_t mlp_pack_train(Ctx &c, hipStream_t s);
 hipError_t launch_features(const Ctx &c, int64_t n, const float *x, const float *y, const float *z, float *feat,
                            hipStream_t s);
 hipError_t mlp_forward_batch(Ctx &c, int64_t m, const float *feat, int64_t rows, const int64_t *idx, float *y,

@@ -1186,15 +1186,15 @@ hipError_t mlp_reserve(Ctx &c, int64_t M)
     return hipSuccess;
 }
 
-// The packed training operands follow the parameters: Adam refreshes them as
-// it goes, a load leaves them to the next training call.
-static void pack_train_if_stale(Ctx &c, hipStream_t s)
+// Packs the parameters into the training kernels' operands (the image follows
+// the parameters at all times: the update refreshes it as it goes, a load packs
+// it anew, so every pass, captured or not, reads the current weights).
+hipError_t mlp_pack_train(Ctx &c, hipStream_t s)
 {
     Mlp &net = c.mlp;
-    if (net.train_version == net.version) return;
     hipLaunchKernelGGL(k_pack_train, dim3((kMlpParams + kBlock - 1) / kBlock), dim3(kBlock), 0, s, net.params,
                        static_cast<__bf16 *>(net.train_image));
-    net.train_version = net.version;
+    return hipGetLastError();
 }
 
 hipError_t mlp_forward_batch(Ctx &c, int64_t M, const float *feat, int64_t rows, const int64_t *idx, float *Yout,
@@ -1202,7 +1202,6 @@ hipError_t mlp_forward_batch(Ctx &c, int64_t M, const float *feat, int64_t rows,
 {
     if (M == 0) return hipSuccess;
     Mlp &net = c.mlp;
-    pack_train_if_stale(c, s);
     hipLaunchKernelGGL(k_mlp_pass<false>, dim3((unsigned)((M + 15) / 16)), dim3(64 * kPassWaves), 0, s, M, feat,
                        rows, idx, net.norm, net.params, static_cast<const uint4 *>(net.train_image), nullptr, 0.0f, Yout,
                        TrainBufs{}, c.err);
@@ -1214,7 +1213,6 @@ static TrainBufs launch_train_pass(Ctx &c, int64_t M, const float *feat, const f
                                    const int64_t *idx, float mu, hipStream_t s)
 {
     Mlp &net = c.mlp;
-    pack_train_if_stale(c, s);
     const TrainBufs tb = train_bufs(c, M);
     hipLaunchKernelGGL(k_mlp_pass<true>, dim3((unsigned)(tb.Mp / 16)), dim3(64 * kPassWaves), 0, s, M, feat, rows,
                        idx, net.norm, net.params, static_cast<const uint4 *>(net.train_image), target, mu, nullptr, tb, c.err);
@@ -1249,7 +1247,6 @@ hipError_t mlp_train_batch(Ctx &c, int64_t M, const float *feat, const float *ta
     ad.c2 = (float)(1.0 - std::pow(b2, (double)net.adam_step));
     hipLaunchKernelGGL(k_mlp_update<true>, dim3(kUpdateBlocks), dim3(kUpdateBlock), 0, s, tb, nullptr, ad, loss);
     net.version += 1;
-    net.train_version = net.version;
     return hipGetLastError();
 }
 
