@@ -92,6 +92,23 @@ __device__ __forceinline__ bool grad_coef(const Weight &Wt, T tau, GradCoef<T> &
     return true;
 }
 
+// phi_k (returned) and its physical derivatives at the node with offsets s,
+// weights w and weight derivatives wd along the axes.
+template <typename T>
+__device__ __forceinline__ T node_phi(const GradCoef<T> &q, T sx, T sy, T sz, T wx, T wy, T wz, T dx, T dy, T dz,
+                                      T dph[3])
+{
+    const T W = wx * wy * wz;
+    const T gp = q.gam[0] + q.gam[1] * sx + q.gam[2] * sy + q.gam[3] * sz;
+    const T dW[3] = {-dx * wy * wz, -wx * dy * wz, -wx * wy * dz};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const T cp = q.cd[d][0] + q.cd[d][1] * sx + q.cd[d][2] * sy + q.cd[d][3] * sz;
+        dph[d] = (dW[d] * gp + W * cp) * q.rH[d];
+    }
+    return W * gp;
+}
+
 // Visits the 27 support nodes (x fastest) with phi_k and the physical
 // derivatives; the loops unroll fully so every index is a constant.  With
 // RECOMPUTE the 1-D weights are evaluated again from the offsets instead of
@@ -106,7 +123,7 @@ __device__ __forceinline__ void for_each_node(const GradCoef<T> &q, const Weight
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const T sx = q.s[0][a], sy = q.s[1][b], sz = q.s[2][c];
-                T wx, wy, wz, dx, dy, dz;
+                T wx, wy, wz, dx, dy, dz, dph[3];
                 if (RECOMPUTE) {
                     weight1_ds(Wt, sx, wx, dx);
                     weight1_ds(Wt, sy, wy, dy);
@@ -115,16 +132,32 @@ __device__ __forceinline__ void for_each_node(const GradCoef<T> &q, const Weight
                     wx = q.w[0][a]; wy = q.w[1][b]; wz = q.w[2][c];
                     dx = q.wd[0][a]; dy = q.wd[1][b]; dz = q.wd[2][c];
                 }
-                const T W = wx * wy * wz;
-                const T gp = q.gam[0] + q.gam[1] * sx + q.gam[2] * sy + q.gam[3] * sz;
-                const T dW[3] = {-dx * wy * wz, -wx * dy * wz, -wx * wy * dz};
-                T dph[3];
+                const T ph = node_phi(q, sx, sy, sz, wx, wy, wz, dx, dy, dz, dph);
+                f(a, b, c, ph, dph);
+            }
+        }
+    }
+}
+
+// The same nodes in the same order with a loop over the z layers, f(a, b, z[c],
+// ...): nine nodes of FP64 state are live at a time.  With all 27 unrolled the
+// kernel below kept 276 to 524 bytes a lane in scratch.
+template <typename F>
+__device__ __forceinline__ void for_each_node_layer(const GradCoef<double> &q, const int64_t z[3], F &&f)
+{
+#pragma unroll 1
+    for (int c = 0; c < 3; ++c) {
+        auto at = [c](const auto v[3]) { return c == 0 ? v[0] : (c == 1 ? v[1] : v[2]); };
+        const double sz = at(q.s[2]), wz = at(q.w[2]), dz = at(q.wd[2]);
+        const int64_t zc = at(z);
 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const T cp = q.cd[d][0] + q.cd[d][1] * sx + q.cd[d][2] * sy + q.cd[d][3] * sz;
-                    dph[d] = (dW[d] * gp + W * cp) * q.rH[d];
-                }
-                f(a, b, c, W * gp, dph);
+        for (int b = 0; b < 3; ++b) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                double dph[3];
+                const double ph = node_phi(q, q.s[0][a], q.s[1][b], sz, q.w[0][a], q.w[1][b], wz, q.wd[0][a],
+                                           q.wd[1][b], dz, dph);
+                f(a, b, zc, ph, dph);
             }
         }
     }
@@ -177,10 +210,14 @@ __device__ __forceinline__ bool build_grad_fp64(const Grid &g, const Weight &Wt,
     return ok;
 }
 
-// Value and gradient: out[0] = sum phi q, out[1 + d] = sum dphi_d q.
+// Value and gradient: out[0] = sum phi q, out[1 + d] = sum dphi_d (q - q0).
+// q0 = 0 for a pair above the routing threshold.  For one that FP32 solved to a
+// result that is not finite, q0 is the home value, the terms of the FP32 sums:
+// an infinite or NaN field value passes through them as it does there, and
+// sums that only FP32 cannot hold come out finite.
 __device__ __forceinline__ bool interp_grad_fp64(const Grid &g, const Weight &Wt, int c, double px, double py,
                                               double pz, const float *fq, const int64_t ox[3], const int64_t oy[3],
-                                              const int64_t oz[3], float out[4])
+                                              const int64_t oz[3], double q0, float out[4])
 {
     const double p[3] = {px, py, pz};
     GradCoef<double> qd;
@@ -188,35 +225,15 @@ __device__ __forceinline__ bool interp_grad_fp64(const Grid &g, const Weight &Wt
     float kmax = 0.f;
     const bool ok = grad_coef(Wt, 0.0, qd, kmax);
     double ad = 0.0, gd[3] = {0.0, 0.0, 0.0};
-    for_each_node<true>(qd, Wt, [&](int a, int b, int cz, double ph, const double dv[3]) {
-        const double fv = (double)fq[oz[cz] + oy[b] + ox[a]];
+    for_each_node_layer(qd, oz, [&](int a, int b, int64_t z0, double ph, const double dv[3]) {
+        const double fv = (double)fq[z0 + oy[b] + ox[a]], df = fv - q0;
         ad += ph * fv;
-        gd[0] += dv[0] * fv; gd[1] += dv[1] * fv; gd[2] += dv[2] * fv;
+        gd[0] += dv[0] * df; gd[1] += dv[1] * df; gd[2] += dv[2] * df;
     });
     const float nan = __builtin_nanf("");
     out[0] = ok ? (float)ad : nan;
     for (int d = 0; d < 3; ++d) out[1 + d] = ok ? (float)gd[d] : nan;
     return ok;
-}
-
-// The same in FP32, for a support with a field value that is not finite: the
-// value summed over q_k, the gradient over q_k - q_home, node by node.
-__device__ __forceinline__ void interp_grad_direct(const Grid &g, const Weight &Wt, float tau, int c,
-                                                   const double p[3], const float *fq, const int64_t ox[3],
-                                                   const int64_t oy[3], const int64_t oz[3], float out[4])
-{
-    GradCoef<float> q;
-    int ih[3];
-    float kmax = 0.f;
-    grad_geo(g, c, p, q, ih);
-    grad_coef(Wt, tau, q, kmax);   // solved in FP32 by the first kernel
-    const float fh = fq[oz[1] + oy[1] + ox[1]];
-    for (int i = 0; i < 4; ++i) out[i] = 0.f;
-    for_each_node<false>(q, Wt, [&](int a, int b, int cz, float ph, const float dv[3]) {
-        const float fv = fq[oz[cz] + oy[b] + ox[a]], df = fv - fh;
-        out[0] += ph * fv;
-        out[1] += dv[0] * df; out[2] += dv[1] * df; out[3] += dv[2] * df;
-    });
 }
 
 __device__ __forceinline__ void count_fp64(DevStats *stats, unsigned long long routed)
@@ -491,7 +508,7 @@ k_interp_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const floa
                    const float *__restrict__ y, const float *__restrict__ z, const float *__restrict__ u,
                    const float *__restrict__ v, const float *__restrict__ w, const float *__restrict__ pf,
                    float *__restrict__ val, float *__restrict__ grad, float *__restrict__ pval,
-                   float *__restrict__ pgrad, uint32_t *queue, float tau, ErrWord *err)
+                   float *__restrict__ pgrad, uint32_t *queue, ErrWord *err)
 {
     const Grid &g = *gp;
     const uint32_t cnt = queue[0];
@@ -518,8 +535,8 @@ k_interp_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const floa
         }
         const float *fq = c == 0 ? u : (c == 1 ? v : (c == 2 ? w : pf));
         float o4[4];
-        if (e & kDirect) interp_grad_direct(g, Wt, tau, c, p, fq, ox, oy, oz, o4);
-        else if (!interp_grad_fp64(g, Wt, c, p[0], p[1], p[2], fq, ox, oy, oz, o4)) raise_error(err, l, MLS_E_SINGULAR);
+        const double q0 = e & kDirect ? (double)fq[oz[1] + oy[1] + ox[1]] : 0.0;
+        if (!interp_grad_fp64(g, Wt, c, p[0], p[1], p[2], fq, ox, oy, oz, q0, o4)) raise_error(err, l, MLS_E_SINGULAR);
         float *vo = c < 3 ? val : pval;
         float *go = c < 3 ? grad + (int64_t)3 * c * n : pgrad;
         if (vo) vo[c < 3 ? (int64_t)c * n + l : l] = o4[0];
@@ -587,7 +604,7 @@ hipError_t launch_interp_grad(Ctx &c, int64_t n, const float *x, const float *y,
         hipLaunchKernelGGL(k_interp_grad<3>, grid, dim3(kGradBlock), 0, s, c.d_grid, c.w, (float)c.opts.kappa_tau, n, x,
                            y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err, c.stats);
     hipLaunchKernelGGL(k_interp_grad_fp64, dim3(round_up8(c.cu_count)), dim3(kGradBlock), 0, s, c.d_grid, c.w, n, x,
-                       y, z, u, v, w, p, U, G, P, GP, c.grad_queue, (float)c.opts.kappa_tau, c.err);
+                       y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err);
     return hipGetLastError();
 }
 
