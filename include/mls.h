@@ -252,7 +252,11 @@ mls_status mls_build_grad(mls_ctx *ctx, int64_t n, const float *x, const float *
  * G[3c + d][l] = d u_c / d x_d ([9][n]); if p != NULL (device FP32 cell-centred
  * field, [n_z][n_y][n_x] over the cells) also P[l] = p at the marker and
  * GP[d][l] = d p / d x_d (either may be NULL).  Same arithmetic and errors as
- * mls_build_grad. */
+ * mls_build_grad; a pair whose FP32 result is not finite is redone in FP64.
+ * The pairs redone go through a queue in the context: mls_build_grad and
+ * mls_interp_grad calls on one context have to be ordered (one stream, or
+ * synchronised in between).  What calls that overlap nevertheless append past
+ * its end is left out and reported as MLS_E_HIP. */
 mls_status mls_interp_grad(mls_ctx *ctx, int64_t n, const float *x, const float *y, const float *z,
                            const float *u, const float *v, const float *w, float *U, float *G, const float *p,
                            float *P, float *GP, void *stream);
@@ -272,7 +276,7 @@ mls_status mls_interp_grad(mls_ctx *ctx, int64_t n, const float *x, const float 
  * order and scheduling, bit for bit.  Device errors (mls_sync, lowest marker
  * first): a marker with a non-finite coordinate or outside a wall axis raises
  * MLS_E_SUPPORT, a body id out of range MLS_E_ARG; such markers are left out
- * and get flag 0.  Cost O(n): three cell lookups per marker, one
+ * and get flag 0.  Cost O(n): three cell lookups per marker and at most one
  * compare-and-swap. */
 mls_status mls_collide(mls_ctx *ctx, int64_t n, const float *x, const float *y, const float *z,
                        const int32_t *body, int32_t *coll, uint8_t *flags, void *stream);

@@ -243,22 +243,27 @@ __device__ __forceinline__ void count_fp64(DevStats *stats, unsigned long long r
 
 // Queue of the (marker, staggering) pairs that a second kernel redoes: q[0]
 // entries, q[1] the workgroups done with them, q[2 + i] = 4 l + c, with
-// kDirect set for a pair that only needs the sums node by node.  The second
-// kernel leaves both counts at zero for the next call.
+// kDirect set for a pair that FP32 solved to a result that is not finite.  The
+// second kernel leaves both counts at zero for the next call; if a launch of
+// the two fails, the next call clears them first (reserve_queue).
 constexpr int kQueueHead = 2;
 constexpr uint32_t kDirect = 0x80000000u;   // 4 l + c stays below it (at most 0x1fffffff markers)
 
-// Appends e of every lane with on set, one reservation per wavefront; every
-// active lane calls it.
-__device__ __forceinline__ void enqueue(uint32_t *queue, bool on, uint32_t e)
+// Appends e (of marker l) of every lane with on set, one reservation per
+// wavefront; every active lane calls it.  cap entries fit: what calls that
+// overlap on one context would append beyond them is left out and reported.
+__device__ __forceinline__ void enqueue(uint32_t *queue, uint32_t cap, bool on, uint32_t e, int64_t l, ErrWord *err)
 {
     const unsigned long long mask = __ballot(on);
     if (!mask) return;
     const int lane = threadIdx.x & 63, lead = __ffsll((long long)mask) - 1;
     uint32_t slot = 0;
     if (lane == lead) slot = atomicAdd(&queue[0], (uint32_t)__popcll(mask));
-    slot = __shfl(slot, lead);
-    if (on) queue[kQueueHead + slot + __popcll(mask & ((1ull << lane) - 1ull))] = e;
+    slot = __shfl(slot, lead) + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+    if (on) {
+        if (slot < cap) queue[kQueueHead + slot] = e;
+        else raise_error(err, l, MLS_E_HIP);
+    }
 }
 
 __global__ void k_queue_clear(uint32_t *queue)
@@ -280,7 +285,8 @@ __device__ __forceinline__ void queue_done(uint32_t *queue, uint32_t cnt)
 __global__ void __launch_bounds__(kGradBlock)
 k_build_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int c, int64_t n, const float *__restrict__ x,
              const float *__restrict__ y, const float *__restrict__ z, uint32_t *__restrict__ home,
-             float *__restrict__ phi, float *__restrict__ dphi, uint32_t *queue, ErrWord *err, DevStats *stats)
+             float *__restrict__ phi, float *__restrict__ dphi, uint32_t *queue, uint32_t qcap, ErrWord *err,
+             DevStats *stats)
 {
     const Grid &g = *gp;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -319,7 +325,7 @@ k_build_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int c, int64_t n
             });
         } else {
             ++routed;
-            enqueue(queue, true, (uint32_t)(4 * l + c));
+            enqueue(queue, qcap, true, (uint32_t)(4 * l + c), l, err);
         }
     }
     count_fp64(stats, routed);
@@ -419,15 +425,15 @@ __device__ __forceinline__ bool value_and_grad(const Weight &Wt, float tau, cons
 // Bound by the vector ALU.  2.56 M markers of a stretched channel with pressure
 // 0.36 ms, 20,480 markers without 9 us; with the node-by-node sums and all
 // staggerings in one wavefront 0.73 ms and 19 us.  A pair whose result is not
-// finite is queued for the node-by-node sums, which pass an infinite or NaN
-// field value on as they meet it.
+// finite is queued for the FP64 sums, which pass an infinite or NaN field value
+// on as they meet it.
 template <int NC>
 __global__ void __launch_bounds__(kGradBlock)
 k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, const float *__restrict__ x,
               const float *__restrict__ y, const float *__restrict__ z, const float *__restrict__ u,
               const float *__restrict__ v, const float *__restrict__ w, const float *__restrict__ pf,
               float *__restrict__ val, float *__restrict__ grad, float *__restrict__ pval,
-              float *__restrict__ pgrad, uint32_t *queue, ErrWord *err, DevStats *stats)
+              float *__restrict__ pgrad, uint32_t *queue, uint32_t qcap, ErrWord *err, DevStats *stats)
 {
     const Grid &g = *gp;
     const int gw = (int)xcd_block() * (kGradBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -470,12 +476,13 @@ k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, cons
         float qv[kNe];
         load_rows(fq, ih[0], nx, oy, oz, qv);
         float o[4] = {0.f, 0.f, 0.f, 0.f};
-        const bool fp32 = value_and_grad(Wt, tau, s, rH, qv, [&]() { wrap_rows(fq, ih[0], ih[1], ih[2], nx, ny, nz, qv); }, o, kmax);
+        const bool fp32 = value_and_grad(
+            Wt, tau, s, rH, qv, [&]() { wrap_rows(fq, ih[0], ih[1], ih[2], nx, ny, nz, qv); }, o, kmax);
         if (!fp32) ++routed;
         const bool finite = fabsf(o[0]) <= 3.0e38f && fabsf(o[1]) <= 3.0e38f && fabsf(o[2]) <= 3.0e38f &&
                             fabsf(o[3]) <= 3.0e38f;
         // the second kernel writes what is queued
-        enqueue(queue, !fp32 || !finite, (uint32_t)(4 * l + c) | (fp32 ? kDirect : 0u));
+        enqueue(queue, qcap, !fp32 || !finite, (uint32_t)(4 * l + c) | (fp32 ? kDirect : 0u), l, err);
         if (vo) vo[l] = o[0];
         if (go) { go[l] = o[1]; go[n + l] = o[2]; go[2 * n + l] = o[3]; }
     }
@@ -486,10 +493,10 @@ k_interp_grad(const Grid *__restrict__ gp, Weight Wt, float tau, int64_t n, cons
 __global__ void __launch_bounds__(kGradBlock)
 k_build_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const float *__restrict__ x,
                   const float *__restrict__ y, const float *__restrict__ z, float *__restrict__ phi,
-                  float *__restrict__ dphi, uint32_t *queue, ErrWord *err)
+                  float *__restrict__ dphi, uint32_t *queue, uint32_t qcap, ErrWord *err)
 {
     const Grid &g = *gp;
-    const uint32_t cnt = queue[0];
+    const uint32_t cnt = min(queue[0], qcap);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
         const uint32_t e = queue[kQueueHead + i];
         const int64_t l = e >> 2;
@@ -508,15 +515,15 @@ k_interp_grad_fp64(const Grid *__restrict__ gp, Weight Wt, int64_t n, const floa
                    const float *__restrict__ y, const float *__restrict__ z, const float *__restrict__ u,
                    const float *__restrict__ v, const float *__restrict__ w, const float *__restrict__ pf,
                    float *__restrict__ val, float *__restrict__ grad, float *__restrict__ pval,
-                   float *__restrict__ pgrad, uint32_t *queue, ErrWord *err)
+                   float *__restrict__ pgrad, uint32_t *queue, uint32_t qcap, ErrWord *err)
 {
     const Grid &g = *gp;
-    const uint32_t cnt = queue[0];
+    const uint32_t cnt = min(queue[0], qcap);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
         const uint32_t e = queue[kQueueHead + i];
         const int64_t l = (e & ~kDirect) >> 2;
         const int c = (int)(e & 3u);
-        if (l >= n) continue;
+        if (l >= n || (c == 3 && !pf)) continue;
         const double p[3] = {(double)x[l], (double)y[l], (double)z[l]};
         int ih[3];
 #pragma unroll
@@ -554,21 +561,38 @@ unsigned grad_blocks(const Ctx &c, int64_t work)
 
 }  // namespace
 
-// The queue holds up to 4 n entries (one per marker and staggering).
+// The queue holds up to 4 n entries (one per marker and staggering).  Its
+// counts are cleared before the first use, on growth and after a failed launch;
+// the stream is waited for then, so that they are clear for a call on any
+// stream (and a capture, whose replays would clear them instead, is refused).
 static hipError_t reserve_queue(Ctx &c, int64_t n, hipStream_t s)
 {
     const int64_t need = kQueueHead + 4 * n;
-    if (need <= c.grad_queue_cap) return hipSuccess;
+    if (need <= c.grad_queue_cap && c.grad_queue_clear) return hipSuccess;
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    hipFree(c.grad_queue);
-    c.grad_queue = nullptr;
-    c.grad_queue_cap = 0;
-    e = hipMalloc((void **)&c.grad_queue, (size_t)need * sizeof(uint32_t));
-    if (e != hipSuccess) return e;
-    c.grad_queue_cap = need;
+    c.grad_queue_clear = false;
+    if (need > c.grad_queue_cap) {
+        hipFree(c.grad_queue);
+        c.grad_queue = nullptr;
+        c.grad_queue_cap = 0;
+        e = hipMalloc((void **)&c.grad_queue, (size_t)need * sizeof(uint32_t));
+        if (e != hipSuccess) return e;
+        c.grad_queue_cap = need;
+    }
     hipLaunchKernelGGL(k_queue_clear, dim3(1), dim3(64), 0, s, c.grad_queue);
-    return hipGetLastError();
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    c.grad_queue_clear = e == hipSuccess;
+    return e;
+}
+
+// The status of a call's launches.
+static hipError_t queue_status(Ctx &c)
+{
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) c.grad_queue_clear = false;
+    return e;
 }
 
 hipError_t launch_build_grad(Ctx &c, int64_t n, const float *x, const float *y, const float *z, int stagger,
@@ -577,12 +601,14 @@ hipError_t launch_build_grad(Ctx &c, int64_t n, const float *x, const float *y, 
     if (n == 0) return hipSuccess;
     hipError_t e = reserve_queue(c, n, s);
     if (e != hipSuccess) return e;
+    const uint32_t qcap = (uint32_t)(c.grad_queue_cap - kQueueHead);
     const int64_t npad = (n + kLanes - 1) / kLanes * kLanes;
     hipLaunchKernelGGL(k_build_grad, dim3(grad_blocks(c, npad)), dim3(kGradBlock), 0, s, c.d_grid, c.w,
-                       (float)c.opts.kappa_tau, stagger, n, x, y, z, home, phi, dphi, c.grad_queue, c.err, c.stats);
+                       (float)c.opts.kappa_tau, stagger, n, x, y, z, home, phi, dphi, c.grad_queue, qcap, c.err,
+                       c.stats);
     hipLaunchKernelGGL(k_build_grad_fp64, dim3(round_up8(c.cu_count)), dim3(kGradBlock), 0, s, c.d_grid, c.w, n, x, y,
-                       z, phi, dphi, c.grad_queue, c.err);
-    return hipGetLastError();
+                       z, phi, dphi, c.grad_queue, qcap, c.err);
+    return queue_status(c);
 }
 
 hipError_t launch_interp_grad(Ctx &c, int64_t n, const float *x, const float *y, const float *z, const float *u,
@@ -592,6 +618,7 @@ hipError_t launch_interp_grad(Ctx &c, int64_t n, const float *x, const float *y,
     if (n == 0) return hipSuccess;
     hipError_t e = reserve_queue(c, n, s);
     if (e != hipSuccess) return e;
+    const uint32_t qcap = (uint32_t)(c.grad_queue_cap - kQueueHead);
     // three or four wavefronts per 64 markers, a multiple of 24 workgroups (8 XCDs)
     const int nc = p ? 4 : 3;
     int64_t blocks = ((n + 63) / 64 * nc + kGradBlock / 64 - 1) / (kGradBlock / 64);
@@ -599,13 +626,13 @@ hipError_t launch_interp_grad(Ctx &c, int64_t n, const float *x, const float *y,
     const dim3 grid((unsigned)((blocks + kBuildGridMultiple - 1) / kBuildGridMultiple * kBuildGridMultiple));
     if (p)
         hipLaunchKernelGGL(k_interp_grad<4>, grid, dim3(kGradBlock), 0, s, c.d_grid, c.w, (float)c.opts.kappa_tau, n, x,
-                           y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err, c.stats);
+                           y, z, u, v, w, p, U, G, P, GP, c.grad_queue, qcap, c.err, c.stats);
     else
         hipLaunchKernelGGL(k_interp_grad<3>, grid, dim3(kGradBlock), 0, s, c.d_grid, c.w, (float)c.opts.kappa_tau, n, x,
-                           y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err, c.stats);
+                           y, z, u, v, w, p, U, G, P, GP, c.grad_queue, qcap, c.err, c.stats);
     hipLaunchKernelGGL(k_interp_grad_fp64, dim3(round_up8(c.cu_count)), dim3(kGradBlock), 0, s, c.d_grid, c.w, n, x,
-                       y, z, u, v, w, p, U, G, P, GP, c.grad_queue, c.err);
-    return hipGetLastError();
+                       y, z, u, v, w, p, U, G, P, GP, c.grad_queue, qcap, c.err);
+    return queue_status(c);
 }
 
 }  // namespace mls

@@ -225,6 +225,7 @@ struct Ctx {
     // derivative shape functions: queue of (marker, staggering) pairs for the FP64 route
     uint32_t *grad_queue = nullptr;
     int64_t grad_queue_cap = 0;
+    bool grad_queue_clear = false;     // its counts are zero between calls
     // time step
     unsigned long long *step_ctr = nullptr;
     int64_t step_sorted_n = -1;   // markers of the last exact step (its rows are in tile order)
