@@ -144,7 +144,7 @@ mls_status mls::setup_tiles(Ctx &c, int want)
 
 bool mls::reserve_stage(Ctx &c)
 {
-    const int64_t per = stage_floats(c, 1), tiles = std::min(c.g.ntiles, c.cap_markers);
+    const int64_t per = stage_floats(c.g, 1), tiles = std::min(c.g.ntiles, c.cap_markers);
     const int64_t need = per * std::min(tiles, kStageBytes / (int64_t)sizeof(float) / per);
     if (need <= c.stage_floats) return true;
     hipFree(c.stage);

@@ -33,7 +33,7 @@ constexpr uint32_t kMaskI = (1u << kPackI) - 1, kMaskJ = (1u << kPackJ) - 1;
 constexpr int kShards = 8;
 constexpr __host__ __device__ int kCursor(int colour, int shard) { return 64 + (colour * kShards + shard) * 32; }
 // Staging buffer of the spreading in two launches: the boxes of 4200 tiles of
-// eight cells.  Up to that many tiles it is faster than one launch per colour.
+// eight cells (spread_staged says when it is used).
 constexpr int64_t kStageBytes = 64ll << 20;
 constexpr int kWorkWords = 64 + 27 * kShards * 32;
 
@@ -324,7 +324,8 @@ hipError_t launch_build_interp(const Ctx &c, int64_t n, const float *x, const fl
 // again: the sort has been spread before (the autotuner times shapes on it).
 hipError_t launch_spread_sorted(Ctx &c, int64_t n, const uint32_t *home, const float *phi, float *fx, float *fy,
                                 float *fz, hipStream_t s, bool again = false);
-int64_t stage_floats(const Ctx &c, int64_t tiles);
+int64_t stage_floats(const Grid &g, int64_t tiles);
+bool spread_staged(const Grid &g, int64_t n);
 // Dynamic LDS of a spreading tile workgroup: the int64 box of one component.
 size_t spread_lds_bytes(const Ctx &c);
 

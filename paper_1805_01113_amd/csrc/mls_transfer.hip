@@ -15,6 +15,7 @@
 // The fixed-point scale of a tile is a power of two chosen from the largest
 // |c_l F_l| (eq. 8) among the tile's markers, so that no sum can overflow and
 // the quantum follows the tile's own forces.
+#include <cmath>
 #include <mutex>
 
 #include "mls_exact.h"
@@ -1040,9 +1041,35 @@ size_t spread_lds_bytes(const Ctx &c)
 }
 
 // Floats of the staged boxes of `tiles` tiles, three components each.
-int64_t stage_floats(const Ctx &c, int64_t tiles)
+int64_t stage_floats(const Grid &g, int64_t tiles)
 {
-    return tiles * 3 * c.g.box[0] * c.g.box[1] * c.g.box[2];
+    return tiles * 3 * g.box[0] * g.box[1] * g.box[2];
+}
+
+// Whether n markers are spread in two launches through the staging buffer
+// rather than in one per colour.  The boxes of all tiles that can hold markers
+// have to fit it.  Then a colour launch costs about 10 us, whatever is in it;
+// the staged route costs 0.08 us a tile with markers (its three boxes go through
+// memory) and 4.4 ns a tile that could have some (its workgroups start and find
+// none), so the line lies at 150 tiles a colour, 18 of the latter for one.  How
+// many tiles hold markers the host does not know; it takes 96 markers a tile of
+// 8^3 cells and 1.5 times the 2/3 power of the cells in general, as for closed
+// surfaces of markers 0.8 cells apart (70 for the smallest particles, 150 for
+// large ones).  Whole exact steps, staged / colours, us: 8 colours, particles of
+// 320 markers in 128^3, 32000 markers 97 / 108, 64000 121 / 113, 128000
+// 164 / 127; of 1280 64000 106 / 117, 128000 139 / 136; of 5120 102400 127 / 126;
+// packed, all 1728 tiles of 96^3 186 / 142, all 4096 of 128^3 378 / 207; 12
+// colours, 141440 markers 152 / 170; 27 colours, 134400 140 / 272.  4-cell tiles
+// in 96^3: 4000 markers 76 / 96, 16000 148 / 96.  (Markers scattered singly over
+// the box fill more tiles than that: 16000 in 128^3 320 / 139.)
+bool spread_staged(const Grid &g, int64_t n)
+{
+    const int colours = g.ncol[0] * g.ncol[1] * g.ncol[2];
+    const int64_t most = std::min(g.ntiles, n);
+    if (colours <= 2 || stage_floats(g, most) > kStageBytes / (int64_t)sizeof(float)) return false;
+    const double cells = (double)g.ax[0].tile * g.ax[1].tile * g.ax[2].tile;
+    const double full = std::min((double)most, (double)n / (1.5 * std::cbrt(cells * cells)));
+    return full + (double)most / 18.0 <= 150.0 * colours;
 }
 
 // Device buffers of one spreading call: the context's own (mls_spread, the
@@ -1068,11 +1095,8 @@ static hipError_t launch_tiles_bx(Ctx &c, const SpreadScratch &sc, int64_t n, co
                                   const float *phi, float *fx, float *fy, float *fz, hipStream_t s, bool timed)
 {
     const size_t lds = spread_lds_bytes(c);
-    // few tiles: two launches through the staging buffer instead of one per
-    // colour (with one or two colours there is nothing to save)
     const int64_t tiles = std::min(c.g.ntiles, n);
-    const int colours = c.g.ncol[0] * c.g.ncol[1] * c.g.ncol[2];
-    const bool staged = sc.tile_slot && colours > 2 && stage_floats(c, tiles) <= sc.stage_floats;
+    const bool staged = sc.tile_slot && spread_staged(c.g, n) && stage_floats(c.g, tiles) <= sc.stage_floats;
     if (lds > 64 * 1024) {
         const void *k = staged ? (const void *)k_spread_stage<SORTED, NF, BX>
                                : (const void *)k_spread_colour<SORTED, NF, BX>;
