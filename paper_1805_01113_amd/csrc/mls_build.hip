@@ -693,19 +693,24 @@ k_table_build(const Weight W, int64_t count, int nsub, const double *__restrict_
 // markers, at most blocks_per_cu per compute unit (the rest is covered by the
 // grid stride), rounded up to a multiple of 24 (8 XCDs x 3 components).
 // A wavefront's first item waits for its operands, the next ones' are requested
-// ahead; so where a full grid would leave a wavefront fewer than 16 items, only
-// the `resident` workgroups per compute unit that run at once are started and
-// stride over all items: 2.56e6 markers of the channel 849 -> 793 us a step
-// (3.7 workgroups per compute unit, a second round for a few: 898), 1.28e6 on a
-// uniform grid 394 -> 377.  With more items many short-lived workgroups keep
-// neighbouring rows together in time: 22.4e6 markers 4440 us, resident only 4540.
+// ahead; so where a grid of kBuildFull per compute unit would leave a wavefront
+// fewer than 16 items, only the `resident` workgroups per compute unit that run
+// at once are started (or blocks_per_cu, if that is less) and stride over all
+// items: 2.56e6 markers of the channel 849 -> 793 us a step (3.7 workgroups per
+// compute unit, a second round for a few: 898), 1.28e6 on a uniform grid 394 ->
+// 377.  With more items many short-lived workgroups keep neighbouring rows
+// together in time: 22.4e6 markers 4300 us, resident only 4470.  The line, 11.2e6
+// markers, lies where both take the same time within the runs' spread (compact
+// steps of 9e6 1853 resident / 1924, 11.2e6 2360 / 2328, 13.4e6 2713 / 2752,
+// 17.9e6 3495 / 3564).
+constexpr int kBuildFull = 32;
 int build_grid(int64_t n, int cu, int blocks_per_cu, int resident)
 {
     const int64_t items = (n + 63) / 64;
     int64_t b = (3 * items + kBuildWaves - 1) / kBuildWaves;
     const int64_t cap = (int64_t)cu * blocks_per_cu;
     const int64_t once = (int64_t)cu * resident / kBuildGridMultiple * kBuildGridMultiple;
-    if (b > once && once > 0 && b < 16 * cap) b = once;
+    if (b > once && once > 0 && b < 16 * (int64_t)cu * kBuildFull) b = once;
     if (b > cap) b = cap;
     if (b < 1) b = 1;
     return (int)((b + kBuildGridMultiple - 1) / kBuildGridMultiple * kBuildGridMultiple);
