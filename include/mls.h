@@ -462,9 +462,10 @@ mls_status mls_timing_get(mls_ctx *ctx, mls_timing *out, int32_t reset);
  * spreading tile launches (bounded further by the LDS of a tile's boxes), of
  * the exact / fast build and of the interpolation; a grid-stride loop covers
  * the work beyond the grid, and a build of few items starts fewer.
- * spread_threads (128, 192 or 256): threads of a
- * spreading tile workgroup (fewer suit many tiles per workgroup, more suit
- * few). */
+ * spread_threads (128, 192 or 256): threads of a spreading tile workgroup
+ * (fewer suit many tiles per workgroup, more suit few).  Few tiles are spread
+ * in two launches with workgroups of their own, which spread_blocks_per_cu and
+ * spread_threads do not change. */
 typedef struct {
     int32_t spread_tile;
     int32_t spread_blocks_per_cu;
@@ -496,8 +497,10 @@ mls_status mls_tune_set(mls_ctx *ctx, const mls_tune *in);
  * are for (MLS_STEP_COMPACT times the compact exact build and spreading; other
  * methods ignore it; other bits: MLS_E_ARG).  cache_path (may be NULL) names a
  * JSON-lines file: an entry whose key (device architecture, compute units,
- * grid, periodic flags, stretched axis, method, flags, floor(log2 n)) matches
- * is applied without timing; otherwise the result is appended.  home, phi, U and
+ * grid, periodic flags, stretched axis, method, flags, floor(log2 n), and which
+ * tile edges spread n markers in two launches) matches is applied without
+ * timing; otherwise the result is appended.  A value that changes nothing for
+ * these buffers (the launches would be the same) keeps its current setting.  home, phi, U and
  * F are overwritten and the forcing fields receive the contributions of the
  * timed spreading calls (zero them afterwards).  Synchronises `stream`. */
 mls_status mls_autotune(mls_ctx *ctx, int32_t method, int32_t flags, const mls_step_buffers *buf,

@@ -44,16 +44,15 @@ int32_t comp_nodes(const Axis &a, int c, int d)
 
 }  // namespace
 
-// Spreading tiles for the requested edge: a periodic axis of at most kMaxTile
-// cells is one tile; a longer one is cut into equal tiles (the requested edge
-// if it divides the axis, else its largest divisor between 4 and
+// Cuts the grid into spreading tiles for the requested edge: a periodic axis of
+// at most kMaxTile cells is one tile; a longer one is cut into equal tiles (the
+// requested edge if it divides the axis, else its largest divisor between 4 and
 // kMaxBoxTile; none -> MLS_E_ARG); a wall axis uses the requested edge.
-// Derives the LDS boxes and the tile colours, (re)allocates the per-tile
-// scratch and uploads the grid.  On error the previous tiling is kept.
-mls_status mls::setup_tiles(Ctx &c, int want)
+// Derives the LDS boxes and the tile colours; colour_tiles (27) receives the
+// tiles of each.
+static mls_status cut_tiles(Grid &g, int want, int64_t colour_tiles[27])
 {
     if (want < 4 || want > kMaxBoxTile) return MLS_E_ARG;
-    Grid g = c.g;
     for (int d = 0; d < 3; ++d) {
         Axis &a = g.ax[d];
         const int n = a.n;
@@ -79,35 +78,51 @@ mls_status mls::setup_tiles(Ctx &c, int want)
     }
     g.ntiles = nt;
     // the fixed-point box of one component must fit the LDS of a workgroup
-    const int64_t lds = (int64_t)g.box[0] * g.box[1] * g.box[2] * 8;
-    if (lds > 160 * 1024) return MLS_E_ARG;
+    if ((int64_t)g.box[0] * g.box[1] * g.box[2] * 8 > 160 * 1024) return MLS_E_ARG;
     // tile colours: tiles whose boxes may overlap get different colours.  Along
     // an axis the colour is the parity of the tile index; an odd number of
     // periodic tiles gives the last tile a third colour.
-    int64_t colour_tiles[27] = {};
-    {
-        int64_t cnt[3][3];
-        for (int d = 0; d < 3; ++d) {
-            const int m = g.ntile[d];
-            const bool periodic = g.ax[d].periodic != 0;
-            g.ncol[d] = m == 1 ? 1 : ((periodic && (m & 1)) ? 3 : 2);
-            if (g.ncol[d] == 1) { cnt[0][d] = 1; cnt[1][d] = 0; cnt[2][d] = 0; }
-            else if (g.ncol[d] == 2) { cnt[0][d] = (m + 1) / 2; cnt[1][d] = m / 2; cnt[2][d] = 0; }
-            else { cnt[0][d] = (m - 1) / 2; cnt[1][d] = (m - 1) / 2; cnt[2][d] = 1; }
-        }
-        for (int k = 0; k < 3; ++k)
-            for (int d = 0; d < 3; ++d) g.ncol_tiles[k][d] = (int32_t)cnt[k][d];
-        for (int k = 0; k < 27; ++k) g.colour_base[k] = 0;
-        int64_t base = 0;
-        for (int cz = 0; cz < g.ncol[2]; ++cz)
-            for (int cy = 0; cy < g.ncol[1]; ++cy)
-                for (int cx = 0; cx < g.ncol[0]; ++cx) {
-                    const int col = cx + g.ncol[0] * (cy + g.ncol[1] * cz);
-                    colour_tiles[col] = cnt[cx][0] * cnt[cy][1] * cnt[cz][2];
-                    g.colour_base[col] = base;
-                    base += colour_tiles[col];
-                }
+    for (int k = 0; k < 27; ++k) colour_tiles[k] = 0;
+    int64_t cnt[3][3];
+    for (int d = 0; d < 3; ++d) {
+        const int m = g.ntile[d];
+        const bool periodic = g.ax[d].periodic != 0;
+        g.ncol[d] = m == 1 ? 1 : ((periodic && (m & 1)) ? 3 : 2);
+        if (g.ncol[d] == 1) { cnt[0][d] = 1; cnt[1][d] = 0; cnt[2][d] = 0; }
+        else if (g.ncol[d] == 2) { cnt[0][d] = (m + 1) / 2; cnt[1][d] = m / 2; cnt[2][d] = 0; }
+        else { cnt[0][d] = (m - 1) / 2; cnt[1][d] = (m - 1) / 2; cnt[2][d] = 1; }
     }
+    for (int k = 0; k < 3; ++k)
+        for (int d = 0; d < 3; ++d) g.ncol_tiles[k][d] = (int32_t)cnt[k][d];
+    for (int k = 0; k < 27; ++k) g.colour_base[k] = 0;
+    int64_t base = 0;
+    for (int cz = 0; cz < g.ncol[2]; ++cz)
+        for (int cy = 0; cy < g.ncol[1]; ++cy)
+            for (int cx = 0; cx < g.ncol[0]; ++cx) {
+                const int col = cx + g.ncol[0] * (cy + g.ncol[1] * cz);
+                colour_tiles[col] = cnt[cx][0] * cnt[cy][1] * cnt[cz][2];
+                g.colour_base[col] = base;
+                base += colour_tiles[col];
+            }
+    return MLS_OK;
+}
+
+bool mls::staged_with_tile(const Ctx &c, int want, int64_t n)
+{
+    Grid g = c.g;
+    int64_t colour_tiles[27];
+    return cut_tiles(g, want, colour_tiles) == MLS_OK && spread_staged(g, n);
+}
+
+// Cuts the tiles, (re)allocates the per-tile scratch and uploads the grid.  On
+// error the previous tiling is kept.
+mls_status mls::setup_tiles(Ctx &c, int want)
+{
+    Grid g = c.g;
+    int64_t colour_tiles[27];
+    const mls_status cut = cut_tiles(g, want, colour_tiles);
+    if (cut != MLS_OK) return cut;
+    const int64_t nt = g.ntiles, lds = (int64_t)g.box[0] * g.box[1] * g.box[2] * 8;
     // device scratch for the new tiling; one extra bucket (index nt) collects
     // markers without a valid support when the step bins markers from their
     // positions

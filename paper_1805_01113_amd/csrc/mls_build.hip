@@ -718,6 +718,16 @@ int build_grid(int64_t n, int cu, int blocks_per_cu, int resident)
 
 }  // namespace
 
+int build_blocks(const Ctx &c, BuildKind kind, int64_t n)
+{
+    // workgroups of the kernel that a compute unit holds; the table look-up
+    // without interpolation starts its full grid
+    const int per_cu = c.build_blocks_per_cu;
+    const int resident = kind == BuildKind::Fast ? per_cu
+                         : kind == BuildKind::ExactStep && c.step_nf == 0 ? 2 : 3;
+    return build_grid(n, c.cu_count, per_cu, resident);
+}
+
 namespace {
 
 int grid_for(int64_t work, int cu)
@@ -735,8 +745,8 @@ hipError_t launch_build_exact(const Ctx &c, int64_t n, const float *x, const flo
 {
     if (n == 0) return hipSuccess;
     const float tau = (float)(c.opts.kappa_tau > 3.0e38 ? 3.0e38 : c.opts.kappa_tau);
-    hipLaunchKernelGGL(k_build_exact, dim3(build_grid(n, c.cu_count, c.build_blocks_per_cu, 3)), dim3(kBuildBlock), 0,
-                       s, c.d_grid, c.w, tau, n, x, y, z, home, phi, route, c.err, c.stats);
+    hipLaunchKernelGGL(k_build_exact, dim3(build_blocks(c, BuildKind::Exact, n)), dim3(kBuildBlock), 0, s,
+                       c.d_grid, c.w, tau, n, x, y, z, home, phi, route, c.err, c.stats);
     return hipGetLastError();
 }
 
@@ -747,7 +757,7 @@ hipError_t launch_build_interp(const Ctx &c, int64_t n, const float *x, const fl
 {
     if (n == 0) return hipSuccess;
     const float tau = (float)(c.opts.kappa_tau > 3.0e38 ? 3.0e38 : c.opts.kappa_tau);
-    const dim3 grid(build_grid(n, c.cu_count, c.build_blocks_per_cu, c.step_nf == 0 ? 2 : 3));
+    const dim3 grid(build_blocks(c, BuildKind::ExactStep, n));
     if (c.step_nf == 0) {
         hipLaunchKernelGGL(k_build_interp<0>, grid, dim3(kBuildBlock), 0, s, c.d_grid, c.w, tau, n, c.entries, x, y, z,
                            home, phi, route, u, v, w, vb, area, 1.0f / dt, U, F, c.cf_rows, c.cf_stride, nullptr,
@@ -787,7 +797,7 @@ hipError_t launch_fast_interp(const Ctx &c, int64_t n, const float *x, const flo
     if (!fast_fused_ok(c)) return hipErrorInvalidValue;
     const int nsub = c.opts.n_sub, nh = (nsub + 1) / 2;
     const size_t lds = (size_t)nh * nh * nh * kTableStride * sizeof(float);
-    const dim3 grid(build_grid(n, c.cu_count, c.build_blocks_per_cu, 3));
+    const dim3 grid(build_blocks(c, BuildKind::FastStep, n));
     const float4 *tab = reinterpret_cast<const float4 *>(c.tables);
     if (trilinear_blend)
         hipLaunchKernelGGL(k_fast_interp<true>, grid, dim3(kBuildBlock), lds, s, c.d_grid, tab, nsub, n, c.entries, x,
@@ -804,7 +814,7 @@ hipError_t launch_build_fast(const Ctx &c, int64_t n, const float *x, const floa
                              uint32_t *home, float *phi, uint8_t *route, hipStream_t s, bool trilinear_blend)
 {
     if (n == 0) return hipSuccess;
-    const dim3 grid(build_grid(n, c.cu_count, c.build_blocks_per_cu, c.build_blocks_per_cu));
+    const dim3 grid(build_blocks(c, BuildKind::Fast, n));
     if (trilinear_blend)
         hipLaunchKernelGGL(k_build_fast<true>, grid, dim3(kBuildBlock), 0, s, c.d_grid, fast_tables(c), n, x, y, z,
                            home, phi, route, c.err);

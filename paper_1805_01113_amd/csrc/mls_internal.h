@@ -250,6 +250,10 @@ struct TimedLaunch {
 
 // ---- launchers (enqueue only; return hipError_t) --------------------------
 
+// Workgroups of a build launch: the stand-alone exact build, those fused into
+// the exact and the fast-MLS step, the stand-alone fast-MLS build.
+enum class BuildKind { Exact, ExactStep, FastStep, Fast };
+int build_blocks(const Ctx &c, BuildKind kind, int64_t n);
 hipError_t launch_build_exact(const Ctx &c, int64_t n, const float *x, const float *y, const float *z,
                               uint32_t *home, float *phi, uint8_t *route, hipStream_t s);
 hipError_t launch_build_fast(const Ctx &c, int64_t n, const float *x, const float *y, const float *z,
@@ -352,6 +356,8 @@ bool reserve_stage(Ctx &c);
 
 // (Re)cut the spreading tiles for edge `want` (see mls_ctx_create).
 mls_status setup_tiles(Ctx &c, int want);
+// Whether n markers would be spread through the staging buffer with that edge.
+bool staged_with_tile(const Ctx &c, int want, int64_t n);
 
 // learned surrogate (training and feature kernels)
 hipError_t mlp_alloc(Ctx &c);

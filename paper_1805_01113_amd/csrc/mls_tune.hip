@@ -45,6 +45,19 @@ double time_call(hipStream_t s, int reps, F fn, bool &ok)
     return best;
 }
 
+// The tile edges tried.
+constexpr int kTiles[] = {4, 6, 8, 10, 12, 16};
+
+// The limits of the staged spreading lie inside octaves of marker counts, and
+// shapes timed on one route say nothing of the other: which of the edges would
+// be spread that way is part of the key where any is (bit i: kTiles[i]).
+unsigned staged_edges(const Ctx &c, int64_t n)
+{
+    unsigned m = 0;
+    for (size_t i = 0; i < sizeof(kTiles) / sizeof(kTiles[0]); ++i) m |= (unsigned)staged_with_tile(c, kTiles[i], n) << i;
+    return m;
+}
+
 std::string tune_key(const Ctx &c, int method, int flags, int64_t n)
 {
     hipDeviceProp_t prop;
@@ -59,7 +72,13 @@ std::string tune_key(const Ctx &c, int method, int flags, int64_t n)
     snprintf(buf, sizeof(buf), "%s|cu%d|%dx%dx%d|p%d%d%d|s%d|m%d|f%d|n%d", arch.c_str(), c.cu_count, c.g.ax[0].n,
              c.g.ax[1].n, c.g.ax[2].n, c.g.ax[0].periodic, c.g.ax[1].periodic, c.g.ax[2].periodic, c.stretched_axis,
              method, flags, oct);
-    return buf;
+    std::string key = buf;
+    const unsigned staged = staged_edges(c, n);
+    if (staged) {
+        snprintf(buf, sizeof(buf), "|t%x", staged);
+        key += buf;
+    }
+    return key;
 }
 
 bool json_int(const std::string &line, const char *name, int &out)
@@ -243,12 +262,18 @@ mls_status mls_autotune(mls_ctx *ctx, int32_t method, int32_t flags, const mls_s
     bool ok = true;
     int cand = 0;
     mls_tune best = cur;
-    // build shapes (the learned build has one workgroup per compute unit)
+    // build shapes (the learned build has one workgroup per compute unit), each
+    // grid once: where several values start the same, the current one stays
     double t_build = 1e30;
-    const int bpcs[] = {8, 16, 32, 64};
+    const int bpcs[] = {cur.build_blocks_per_cu, 8, 16, 32, 64};
+    const BuildKind kind = method == MLS_EXACT ? BuildKind::ExactStep : exact ? BuildKind::FastStep : BuildKind::Fast;
+    std::vector<int> grids;
     if (method != MLS_LEARNED) {
         for (int v : bpcs) {
             c.build_blocks_per_cu = v;
+            const int grid = build_blocks(c, kind, n);
+            if (std::find(grids.begin(), grids.end(), grid) != grids.end()) continue;
+            grids.push_back(grid);
             const double t = time_call(s, 3, build, ok);
             if (!ok) break;
             ++cand;
@@ -275,17 +300,34 @@ mls_status mls_autotune(mls_ctx *ctx, int32_t method, int32_t flags, const mls_s
     if (ok && !exact) ok = launch_force(c, n, b->vb, b->U, 1.0f, b->F, s) == hipSuccess;
     // spreading: tile edge x resident workgroups
     double t_spread = 1e30;
-    const int tiles[] = {4, 6, 8, 10, 12, 16};
     const int spcs[] = {1, 2, 4, 8, 16, 32};
     const int sthreads[] = {128, 192, 256};
     std::vector<std::vector<int>> seen;
-    for (int tile : tiles) {
+    for (int tile : kTiles) {
         if (!ok) break;
         if (setup_tiles(c, tile) != MLS_OK) continue;
         std::vector<int> shape = {c.g.ax[0].tile, c.g.ax[1].tile, c.g.ax[2].tile};
         if (std::find(seen.begin(), seen.end(), shape) != seen.end()) continue;
         seen.push_back(shape);
         if (exact) ok = build() == MLS_OK;   // bin for this tiling (untimed)
+        if (ok && spread_staged(c.g, n)) {
+            // the staged route has workgroups of its own: one candidate, and
+            // the current shape of the colour launches stays
+            c.spread_threads = cur.spread_threads;
+            c.spread_blocks_per_cu_req = cur.spread_blocks_per_cu;
+            c.spread_blocks_per_cu = std::max(1, std::min(cur.spread_blocks_per_cu,
+                                                          (int)((160 * 1024) / ((int64_t)spread_lds_bytes(c) + 512))));
+            const double t = time_call(s, 3, spread, ok);
+            if (!ok) break;
+            ++cand;
+            if (t < t_spread) {
+                t_spread = t;
+                best.spread_tile = tile;
+                best.spread_blocks_per_cu = cur.spread_blocks_per_cu;
+                best.spread_threads = cur.spread_threads;
+            }
+            continue;
+        }
         for (int th : sthreads) {
             int last_eff = -1;
             c.spread_threads = th;
