@@ -461,7 +461,8 @@ k_build_fast(const Grid *__restrict__ gp, const FastTables T, int64_t n,
 // those of the whole-table lookup; a corner in the negative half of an axis
 // reads the row of its mirror image, and the blended nodes of every such axis
 // are put back in place with a layer of conditional swaps.  Three wavefronts
-// per SIMD: with four the kernel spills (207 -> 200 us on 1.28 M markers).
+// per SIMD (142 registers): with four it spills (1.28 M markers 207 us instead of
+// 200; whole steps of 4.5 M to 22.4 M the same or up to 5 % slower).
 template <bool TRILINEAR>
 __global__ void __launch_bounds__(kBuildBlock) __attribute__((amdgpu_waves_per_eu(3)))
 k_fast_interp(const Grid *__restrict__ gp, const float4 *__restrict__ tab, int nsub, int64_t n,

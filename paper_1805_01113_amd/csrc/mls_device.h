@@ -374,8 +374,9 @@ __device__ __forceinline__ void assemble(const Moments<T> mx, const Moments<T> m
 // Cholesky factor of the symmetric 4x4 A (10 entries).  Returns false if A is
 // not numerically positive definite.  L stored row-wise lower: l00 l10 l11
 // l20 l21 l22 l30 l31 l32 l33; the diagonal holds 1/l_ii.
-// (the instruction itself: a denormal pivot, which rsqrtf would rescale, belongs
-// to a matrix that is far beyond the FP32 condition bound anyway)
+// (the instruction itself: it gives infinity for a denormal pivot, which rsqrtf
+// would rescale; the condition bound is then not finite and the pair goes to
+// FP64)
 __device__ __forceinline__ float rsqrt_t(float v) { return __builtin_amdgcn_rsqf(v); }
 __device__ __forceinline__ double rsqrt_t(double v) { return 1.0 / sqrt(v); }
 

@@ -46,9 +46,9 @@ __device__ __forceinline__ bool solve_fp64_regs(const Grid &g, const Weight &W, 
 }
 
 // Stencil for a marker without a support (where ok is false): the uniform
-// node offsets -1, 0, 1 at node 1, whose neighbours every axis has.  The fused kernels compute such a marker
-// like any other (so all lanes issue the same memory operations) and store
-// NaN in its place.  Selects on every field (G may hold anything there), so
+// node offsets -1, 0, 1 at node 1, whose neighbours every axis has.  The fused
+// kernels compute such a marker like any other (so all lanes issue the same
+// memory operations) and store NaN in its place.  Selects on every field (G may hold anything there), so
 // that the compiler does not first set every register to the neutral values
 // and then copy the located ones over them.
 __device__ __forceinline__ void neutral_geo_unless(bool ok, AxisGeo G[3])
