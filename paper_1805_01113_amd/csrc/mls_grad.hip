@@ -12,9 +12,10 @@
 // p_k p_k^T, assembled from separable moments like A itself (the moments of
 // axis d taken with w' in place of w).  The physical derivative divides by
 // H_d.  The solve runs in FP32 with the condition bound of the exact build;
-// a (marker, staggering) above the routing threshold is queued and redone in
-// FP64 from the position by a second kernel, which keeps the registers of the
-// double-precision state off the FP32 kernel.
+// a (marker, staggering) above the routing threshold, or whose interpolated
+// result is not finite, is queued and redone in FP64 from the position by a
+// second kernel, which keeps the registers of the double-precision state off the
+// FP32 kernel.
 #include "mls_device.h"
 
 namespace mls {

@@ -777,10 +777,9 @@ k_spread_colour(const Grid *__restrict__ gp, int colour, const uint32_t *__restr
 // ---- spreading in two launches --------------------------------------------------
 //
 // With few tiles the 8 to 27 colour launches cost more than the work in them
-// (a launch about 4.3 us, and each waits for its slowest tile).  When the boxes
-// of all tiles that can hold markers fit the staging buffer (kStageBytes),
-// every (tile, component) pair accumulates its box at once and stores it there,
-// converted to FP32 as the flush converts it (k_spread_stage); then every node
+// (a launch about 4.3 us, and each waits for its slowest tile).  Where
+// spread_staged says so, every (tile, component) pair accumulates its box at once
+// and stores it in the staging buffer, converted to FP32 as the flush converts it (k_spread_stage); then every node
 // takes its additions from the up to eight boxes that hold it, one after
 // another in the order of the tiles' colours (k_spread_merge): the same
 // additions in the same order as with one launch per colour, bit for bit.

@@ -5,9 +5,10 @@
 // workgroups per compute unit of the build, interpolation and spreading
 // launches.  mls_autotune times candidates of each phase on the caller's own
 // step buffers with HIP events, keeps the fastest and remembers it in a
-// JSON-lines cache keyed by device architecture, compute units, grid, method
-// and marker-count octave, so that a later run on the same kind of device and
-// problem applies the stored shapes without timing.
+// JSON-lines cache keyed by device architecture, compute units, grid, method,
+// marker-count octave and the spreading routes (staged_edges), so that a later
+// run on the same kind of device and problem applies the stored shapes without
+// timing.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
