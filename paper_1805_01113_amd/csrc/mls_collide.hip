@@ -47,7 +47,14 @@ __device__ __forceinline__ int64_t marker_cell(const Grid &g, int64_t l, const f
 // Ids into the cells.  A body id out of range is left out (reported here).
 // entered holds (cell, body) pairs that the workgroup has entered, by a hash of
 // the cell, the newest in its place: a marker that finds its own pair there is
-// done.
+// done.  One that finds another body's pair of its cell looks at the cell before
+// it swaps, and so does a wavefront of whose markers less than half are done
+// (markers next to each other in the array, but not in space): a cell only moves
+// 0 -> id -> -1, so a plain read that shows the marker's id or -1, possibly an
+// earlier state, spares the swap.  Collision, flags and clearing, never looking
+// / so / always looking, us: 22.4 M markers body after body 590 / 593 / 619,
+// shuffled 1918 / 1636 / -; 4 M markers of 1000 bodies at random in 64^3 245 /
+// 163 / -, in 40 cells of it 1243 / 267 / -.
 __global__ void __launch_bounds__(kCollBlock)
 k_coll_enter(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x, const float *__restrict__ y,
              const float *__restrict__ z, const int32_t *__restrict__ body, int32_t *__restrict__ coll,
@@ -60,18 +67,32 @@ k_coll_enter(const Grid *__restrict__ gp, int64_t n, const float *__restrict__ x
     // the workgroup's markers: a contiguous range
     const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 63) & ~(int64_t)63;
     const int64_t first = xcd_block() * per, last = min(first + per, n);
+    int met = 0, known = 0;   // markers of this wavefront, and those whose pair was in the table
     for (int64_t l = first + threadIdx.x; l < last; l += kCollBlock) {
-        const int64_t cell = marker_cell(g, l, x, y, z, err);
-        if (cell < 0) continue;
+        int64_t cell = marker_cell(g, l, x, y, z, err);
         const int32_t b = body[l];
-        if (b < 0 || b > 2147483646) {
+        if (cell >= 0 && (b < 0 || b > 2147483646)) {
             raise_error(err, l, MLS_E_ARG);
-            continue;
+            cell = -1;
         }
-        const unsigned long long pair = (unsigned long long)(uint32_t)cell << 32 | (uint32_t)b;
-        if (atomicExch(&entered[((uint32_t)cell * 2654435761u) >> (32 - kEnteredBits)], pair) == pair) continue;
-        const int32_t old = atomicCAS(&coll[cell], 0, b + 1);
-        if (old != 0 && old != b + 1 && old != -1) atomicExch(&coll[cell], -1);
+        bool done = cell < 0, look = false;
+        if (!done) {
+            const unsigned long long pair = (unsigned long long)(uint32_t)cell << 32 | (uint32_t)b;
+            const unsigned long long was =
+                atomicExch(&entered[((uint32_t)cell * 2654435761u) >> (32 - kEnteredBits)], pair);
+            done = was == pair;
+            look = (was ^ pair) >> 32 == 0;
+        }
+        met += __popcll(__ballot(1));
+        known += __popcll(__ballot(done));
+        if (!done && (look || 2 * known < met)) {
+            const int32_t now = coll[cell];
+            done = now == b + 1 || now == -1;
+        }
+        if (!done) {
+            const int32_t old = atomicCAS(&coll[cell], 0, b + 1);
+            if (old != 0 && old != b + 1 && old != -1) atomicExch(&coll[cell], -1);
+        }
     }
 }
 
